@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kBlock) void round_kernel(int64_t n, int C, int64_t
 // 16 channels, 32 B per cell) is loaded once with coalesced 16-B loads into
 // one slot of a two-slot LDS ring while the other slot is read, one
 // barrier per plane.  Wave w computes output row w as four 16-cell chains.
-constexpr int kCnnTX = 64, kCnnTY = 4, kCnnKC = 16;
+constexpr int kCnnTX = 64, kCnnTY = 4, kCnnKC = 16;  // kCnnKC: at most
 constexpr int kCnnPX = kCnnTX + 2, kCnnPY = kCnnTY + 2;
 constexpr int kCnnPlane = kCnnPX * kCnnPY;  // cells per LDS plane
 // In-plane tap pairs: pair m joins the taps 2m and 2m + 1 of the 3 x 3
@@ -133,6 +133,40 @@ constexpr int kCnnPairs = 5;
 // contiguous reads, while a 48-B stride costs 1.8x.
 constexpr int kCnnCellB = 32;
 
+// Tiles of a launch: 64 x 4 in the plane, chunks of `levels` z levels.  A
+// chunk costs its levels and two planes more, so the longest (16) does the
+// least work; but a grid of few tiles then leaves CUs idle while each block
+// walks its 18 planes.  Two blocks share a CU, so the time goes as the
+// rounds of 512 blocks that the launch takes times the planes of a block;
+// the chunk length with the least of that is taken, the longest on a tie.
+// One 64 x 64 x 64 field (64 blocks at 16 levels, 512 at 2): layers 0 + 1,
+// 2, 3 take 45, 24, 21 us at 16 levels and 19, 11, 9 us at 2.
+// A level's sums run over its three planes in the same order whatever the
+// chunk.
+struct CnnTiling {
+  int tiles_x, tiles_y, chunks, levels;
+};
+inline CnnTiling cnn_tiling(const CnnGeom &G) {
+  CnnTiling C;
+  C.tiles_x = (G.nxo + kCnnTX - 1) / kCnnTX;
+  C.tiles_y = (G.nyo + kCnnTY - 1) / kCnnTY;
+  int64_t best = INT64_MAX;
+  for (int kc = kCnnKC; kc >= 2; --kc) {
+    const int chunks = (G.nz + kc - 1) / kc;
+    const int64_t blocks = (int64_t)G.batch * C.tiles_x * C.tiles_y * chunks;
+    const int64_t cost = (blocks + 511) / 512 * (kc + 2);
+    if (cost < best) {
+      best = cost;
+      C.chunks = chunks;
+      C.levels = kc;
+    }
+  }
+  return C;
+}
+inline unsigned cnn_blocks(const CnnGeom &G, const CnnTiling &C) {
+  return (unsigned)(((int64_t)G.batch * C.tiles_x * C.tiles_y * C.chunks + 7) / 8 * 8);
+}
+
 // Block geometry shared by the tiled layers: a 64 x 4 output tile of batch
 // item b over z levels [k0, k1).  The grid is a multiple of 8 blocks and
 // XCD x (the blocks b with b % 8 = x) takes the x-th contiguous range of
@@ -143,26 +177,24 @@ struct CnnTile {
   int b, ox0, oy0, ix0, iy0, k0, k1;
   bool valid;
 };
-inline unsigned cnn_blocks(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
-__device__ __forceinline__ CnnTile cnn_tile(const CnnGeom &G, int tiles_x, int tiles_y,
-                                            int chunks) {
+__device__ __forceinline__ CnnTile cnn_tile(const CnnGeom &G, const CnnTiling &C) {
   const int per = (int)(gridDim.x >> 3);
   int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
   CnnTile T;
-  T.valid = blk < G.batch * tiles_x * tiles_y * chunks;
+  T.valid = blk < G.batch * C.tiles_x * C.tiles_y * C.chunks;
   if (!T.valid) blk = 0;
-  const int tx = blk % tiles_x;
-  blk /= tiles_x;
-  const int ty = blk % tiles_y;
-  blk /= tiles_y;
-  const int kz = blk % chunks;
-  T.b = blk / chunks;
+  const int tx = blk % C.tiles_x;
+  blk /= C.tiles_x;
+  const int ty = blk % C.tiles_y;
+  blk /= C.tiles_y;
+  const int kz = blk % C.chunks;
+  T.b = blk / C.chunks;
   T.ox0 = tx * kCnnTX;
   T.oy0 = ty * kCnnTY;
   T.ix0 = G.periodic ? T.ox0 - 1 : T.ox0;
   T.iy0 = G.periodic ? T.oy0 - 1 : T.oy0;
-  T.k0 = kz * kCnnKC;
-  T.k1 = min(G.nz, T.k0 + kCnnKC);
+  T.k0 = kz * C.levels;
+  T.k1 = min(G.nz, T.k0 + C.levels);
   return T;
 }
 
@@ -261,15 +293,14 @@ __global__ __launch_bounds__(256, 2) void conv_mid_kernel(
     CnnGeom G, const uint16_t *__restrict__ ain, const float *__restrict__ rin,
     const double *__restrict__ in_scale, const float *__restrict__ bias0,
     const uint16_t *__restrict__ w0, const float *__restrict__ bias,
-    const uint16_t *__restrict__ w, float alpha, uint16_t *__restrict__ aout, int tiles_x,
-    int tiles_y, int chunks) {
+    const uint16_t *__restrict__ w, float alpha, uint16_t *__restrict__ aout, CnnTiling C) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][kCnnPlane * kCnnCellB];
   // fused: the ring of staged input levels, one bfloat16 value per 32-bit
   // word so that every operand read is an aligned word
   __shared__ uint32_t inr[FUSED ? 4 : 1][FUSED ? kInPlane : 1];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int row = lane & 15, quad = lane >> 4, side = quad >> 1, half = quad & 1;
-  const CnnTile T = cnn_tile(G, tiles_x, tiles_y, chunks);
+  const CnnTile T = cnn_tile(G, C);
   if (!T.valid) return;  // the whole block
   auto slot = [&](int p) { return (p - T.k0 + 1) & 1; };  // LDS slot of plane p
 
@@ -503,12 +534,12 @@ __global__ __launch_bounds__(256) void conv_in_kernel(CnnGeom G, const uint16_t 
                                                       const float *__restrict__ params,
                                                       const uint16_t *__restrict__ wbf,
                                                       float alpha, uint16_t *__restrict__ aout,
-                                                      int tiles_x, int tiles_y, int chunks) {
+                                                      CnnTiling C) {
   constexpr int K = kCnnTaps * CI, KM = (K + 15) / 16;
   __shared__ uint16_t lds[3][CI][kCnnPlane];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int row = lane & 15, quad = lane >> 4;
-  const CnnTile T = cnn_tile(G, tiles_x, tiles_y, chunks);
+  const CnnTile T = cnn_tile(G, C);
   if (!T.valid) return;  // the whole block
   // A operands: W0[tap][o = row][c] for k = 16 m + 4 quad + r
   bf16x4 wa[KM];
@@ -605,13 +636,12 @@ __global__ __launch_bounds__(256) void conv_out_kernel(CnnGeom G, const uint16_t
                                                        float *__restrict__ y,
                                                        const T *__restrict__ base,
                                                        const double *__restrict__ s_over_d,
-                                                       T *__restrict__ guess, int tiles_x,
-                                                       int tiles_y, int chunks) {
+                                                       T *__restrict__ guess, CnnTiling C) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][kCnnPlane * kCnnCellB];
   __shared__ __attribute__((aligned(16))) float res[4][kCnnTX];  // a finished level per wave
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int row = lane & 15, quad = lane >> 4, side = quad >> 1, half = quad & 1;
-  const CnnTile Tl = cnn_tile(G, tiles_x, tiles_y, chunks);
+  const CnnTile Tl = cnn_tile(G, C);
   if (!Tl.valid) return;  // the whole block
   const uint16_t *w3 = wbf + cnn_weight_offset(G.inputs, 3);
 
@@ -1118,47 +1148,40 @@ void launch_cnn_round(int64_t n, int C, int64_t cells, const float *x, const dou
 
 void launch_cnn_conv(int layer, const CnnGeom &G, const uint16_t *ain, const float *params,
                      const uint16_t *wbf, float alpha, uint16_t *aout, float *yout, hipStream_t s) {
-  const int tiles_x = (G.nxo + kCnnTX - 1) / kCnnTX, tiles_y = (G.nyo + kCnnTY - 1) / kCnnTY;
-  const int chunks = (G.nz + kCnnKC - 1) / kCnnKC;
-  const unsigned blocks = cnn_blocks((int64_t)G.batch * tiles_x * tiles_y * chunks);
+  const CnnTiling C = cnn_tiling(G);
+  const unsigned blocks = cnn_blocks(G, C);
   if (layer == 0) {
     if (G.inputs == 3)
-      conv_in_kernel<3><<<blocks, 256, 0, s>>>(G, ain, params, wbf, alpha, aout, tiles_x, tiles_y,
-                                               chunks);
+      conv_in_kernel<3><<<blocks, 256, 0, s>>>(G, ain, params, wbf, alpha, aout, C);
     else
-      conv_in_kernel<1><<<blocks, 256, 0, s>>>(G, ain, params, wbf, alpha, aout, tiles_x, tiles_y,
-                                               chunks);
+      conv_in_kernel<1><<<blocks, 256, 0, s>>>(G, ain, params, wbf, alpha, aout, C);
   } else if (layer < kCnnLayers - 1) {
     conv_mid_kernel<false><<<blocks, 256, 0, s>>>(
         G, ain, nullptr, nullptr, nullptr, nullptr, params + cnn_bias_offset(G.inputs, layer),
-        wbf + cnn_weight_offset(G.inputs, layer), alpha, aout, tiles_x, tiles_y, chunks);
+        wbf + cnn_weight_offset(G.inputs, layer), alpha, aout, C);
   } else {
     conv_out_kernel<float, false><<<blocks, 256, 0, s>>>(G, ain, params, wbf, yout, nullptr,
-                                                         nullptr, nullptr, tiles_x, tiles_y,
-                                                         chunks);
+                                                         nullptr, nullptr, C);
   }
 }
 
 void launch_cnn_in_mid(const CnnGeom &G, const float *r, const double *scale, const float *params,
                        const uint16_t *wbf, float alpha, uint16_t *aout, hipStream_t s) {
-  const int tiles_x = (G.nxo + kCnnTX - 1) / kCnnTX, tiles_y = (G.nyo + kCnnTY - 1) / kCnnTY;
-  const int chunks = (G.nz + kCnnKC - 1) / kCnnKC;
-  const unsigned blocks = cnn_blocks((int64_t)G.batch * tiles_x * tiles_y * chunks);
+  const CnnTiling C = cnn_tiling(G);
+  const unsigned blocks = cnn_blocks(G, C);
   conv_mid_kernel<true><<<blocks, 256, 0, s>>>(
       G, nullptr, r, scale, params + cnn_bias_offset(1, 0), wbf + cnn_weight_offset(1, 0),
-      params + cnn_bias_offset(1, 1), wbf + cnn_weight_offset(1, 1), alpha, aout, tiles_x, tiles_y,
-      chunks);
+      params + cnn_bias_offset(1, 1), wbf + cnn_weight_offset(1, 1), alpha, aout, C);
 }
 
 template <typename T>
 void launch_cnn_guess(const CnnGeom &G, const uint16_t *ain, const float *params,
                       const uint16_t *wbf, const T *base, const double *s_over_d, T *guess,
                       hipStream_t s) {
-  const int tiles_x = (G.nxo + kCnnTX - 1) / kCnnTX, tiles_y = (G.nyo + kCnnTY - 1) / kCnnTY;
-  const int chunks = (G.nz + kCnnKC - 1) / kCnnKC;
-  const unsigned blocks = cnn_blocks((int64_t)G.batch * tiles_x * tiles_y * chunks);
+  const CnnTiling C = cnn_tiling(G);
+  const unsigned blocks = cnn_blocks(G, C);
   conv_out_kernel<T, true><<<blocks, 256, 0, s>>>(G, ain, params, wbf, nullptr, base, s_over_d,
-                                                  guess, tiles_x, tiles_y, chunks);
+                                                  guess, C);
 }
 
 void launch_cnn_loss(int batch, int nz, int ny, int nx, double wx, double wy, double wz,

@@ -530,3 +530,19 @@ def test_learned3_step_converges(gpu):
     for k in ("u", "v", "w", "thl", "qt", "p"):
         d = out["zero"][k] - out["zero"][k].mean(axis=(1, 2), keepdims=True)
         assert np.linalg.norm(out["learned3"][k] - out["zero"][k]) <= 1e-3 * np.linalg.norm(d)
+
+
+@pytest.mark.parametrize("periodic,nz,ny,nx", [(True, 33, 9, 70), (False, 17, 12, 75),
+                                               (True, 2, 5, 3), (False, 40, 11, 11)])
+def test_forward_does_not_depend_on_the_chunk_length(gpu, periodic, nz, ny, nx):
+    """A small field is cut into short z chunks, a large batch of it into
+    16-level ones: each level's sums are the same, so the outputs are equal
+    bit for bit."""
+    import torch
+    prm = _t(params(3))
+    packed = gpu.pack(prm)
+    x = _t(np.random.default_rng(4).standard_normal((1, nz, ny, nx)))
+    one, _ = gpu.forward(prm, packed, x, periodic=periodic, alpha=0.1)
+    many, _ = gpu.forward(prm, packed, x.repeat(400, 1, 1, 1).contiguous(), periodic=periodic,
+                          alpha=0.1)
+    assert torch.equal(many, one.expand_as(many))
