@@ -115,7 +115,9 @@ typedef struct les_config {
   int32_t poisson_max_sweeps;   /* cap per solve */
   int32_t satadj_maxit;         /* secant iteration cap */
   int32_t sweeps_per_launch;    /* Poisson sweeps fused per kernel launch, 0..2
-                                   (0: default); results do not depend on it */
+                                   (0: default, every sweep of a solve in one
+                                   launch where the grid fits the chip, else 1);
+                                   results do not depend on it */
   double dx, dy, dz, dt;        /* m, m, m, s; all > 0 */
   double poisson_tol;           /* stop when ||rhs - L phi||_2 <= tol ||rhs||_2 */
   double jacobi_omega;          /* 0 selects 2/(mu_min+mu_max) */

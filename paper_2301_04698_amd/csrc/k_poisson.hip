@@ -97,25 +97,29 @@ __global__ __launch_bounds__(kBlock) void level_sum_kernel(Grid g, const T *__re
 // solves that part, (pb_{k+1} - 2 pb_k + pb_{k-1}) / dz^2 = rb_k with
 // rb_k = level mean - m and mirror ghosts: the face gradient is zero at the
 // bottom wall and grows by dz rb_k across level k; pb has zero mean.  One
-// block; the level sums are one wave per level, the running sums
-// sequential in a fixed order over LDS chunks of kScan levels.
-constexpr int kScan = 2048;
-__global__ __launch_bounds__(256) void mean_mode_kernel(const double *__restrict__ part, int lp,
+// block, bound by latency: the level sums are one wave per level, sixteen
+// waves at work, and the running sums, sequential in a fixed order over LDS
+// chunks of kScan levels, take their operands from LDS kAhead at a time (128
+// levels: 25.7 us with four waves and one operand at a time).
+constexpr int kScan = 2048, kMeanThreads = 1024, kMeanSum = 256, kAhead = 8;
+__global__ __launch_bounds__(kMeanThreads) void mean_mode_kernel(const double *__restrict__ part, int lp,
                                                         int nz, double nxy, double dz, int exact,
                                                         SolveCtl *ctl, double *__restrict__ rsub,
                                                         double *__restrict__ pb) {
   __shared__ double buf[kScan];
   __shared__ double bcast;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int k = wv; k < nz; k += 4) {
+  for (int k = wv; k < nz; k += kMeanThreads / 64) {
     double s = 0.0;
     for (int q = lane; q < lp; q += 64) s += part[(int64_t)k * lp + q];
     s = wave_sum(s);
     if (lane == 0) rsub[k] = s / nxy;
   }
   __syncthreads();
+  // sums over levels by the first kMeanSum threads
+  const int k_sum = threadIdx.x < kMeanSum ? (int)threadIdx.x : nz;
   double t = 0.0;
-  for (int k = threadIdx.x; k < nz; k += blockDim.x) t += rsub[k];
+  for (int k = k_sum; k < nz; k += kMeanSum) t += rsub[k];
   t = block_sum(t);
   if (threadIdx.x == 0) {
     bcast = t / nz;
@@ -136,17 +140,19 @@ __global__ __launch_bounds__(256) void mean_mode_kernel(const double *__restrict
     for (int k = c0 + threadIdx.x; k < c1; k += blockDim.x) buf[k - c0] = rsub[k] - m;
     __syncthreads();
     if (threadIdx.x == 0)
-      for (int k = c0; k < c1; ++k) {  // buf: rb_k in, pb_k out
-        const double r = buf[k - c0];
-        buf[k - c0] = p;
-        G += dz * r;
-        p += dz * G;
+      for (int k = c0; k < c1; k += kAhead) {  // buf: rb_k in, pb_k out
+        double r[kAhead];
+        for (int u = 0; u < kAhead; ++u) r[u] = buf[min(k + u, kScan - 1 + c0) - c0];
+        for (int u = 0; u < kAhead; ++u)
+          if (k + u < c1) {
+            buf[k + u - c0] = p;
+            G += dz * r[u];
+            p += dz * G;
+          }
       }
     __syncthreads();
-    for (int k = c0 + threadIdx.x; k < c1; k += blockDim.x) {
-      pb[k] = buf[k - c0];
-      acc += buf[k - c0];
-    }
+    for (int k = c0 + k_sum; k < c1; k += kMeanSum) acc += buf[k - c0];
+    for (int k = c0 + threadIdx.x; k < c1; k += blockDim.x) pb[k] = buf[k - c0];
     __syncthreads();
   }
   acc = block_sum(acc);
@@ -182,11 +188,11 @@ __global__ __launch_bounds__(kBlock) void center_kernel(Grid g, int lp, const T 
 
 // gbar[k] = level mean from the level partials (exact mode), else 0; and
 // gbar[nz] = the overall mean (the mean of the level means).
-__global__ __launch_bounds__(256) void level_mean_kernel(const double *__restrict__ part, int lp,
+__global__ __launch_bounds__(kMeanThreads) void level_mean_kernel(const double *__restrict__ part, int lp,
                                                          int nz, double nxy, int exact,
                                                          double *__restrict__ gbar) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int k = wv; k < nz; k += 4) {
+  for (int k = wv; k < nz; k += kMeanThreads / 64) {
     double s = 0.0;
     if (exact)
       for (int q = lane; q < lp; q += 64) s += part[(int64_t)k * lp + q];
@@ -195,7 +201,8 @@ __global__ __launch_bounds__(256) void level_mean_kernel(const double *__restric
   }
   __syncthreads();
   double t = 0.0;
-  for (int k = threadIdx.x; k < nz; k += blockDim.x) t += gbar[k];
+  if (threadIdx.x < kMeanSum)
+    for (int k = threadIdx.x; k < nz; k += kMeanSum) t += gbar[k];
   t = block_sum(t);
   if (threadIdx.x == 0) gbar[nz] = t / nz;
 }
@@ -625,6 +632,7 @@ __global__ void ctl_restart_kernel(SolveCtl *ctl, int max_sweeps) {
   ctl->stop_m = -1;
   ctl->res_norm2 = 0.0;
   ctl->guess_kept = 0;
+  ctl->aborted = 0;
 }
 
 __global__ void ctl_reset_kernel(SolveCtl *ctl, int max_sweeps, int fixed) {
@@ -639,6 +647,7 @@ __global__ void ctl_reset_kernel(SolveCtl *ctl, int max_sweeps, int fixed) {
   ctl->stop_m = -1;
   ctl->max_sweeps = max_sweeps;
   ctl->fixed = fixed;
+  ctl->aborted = 0;
 }
 
 }  // namespace
@@ -667,12 +676,12 @@ void launch_level_sum(const Grid &g, const T *f, double *part, hipStream_t s) {
 
 void launch_mean_mode(const Grid &g, const double *part, int exact, SolveCtl *ctl, double *rsub,
                       double *pb, hipStream_t s) {
-  mean_mode_kernel<<<1, 256, 0, s>>>(part, level_parts(g), g.nz, (double)g.nxy, g.dz, exact, ctl,
+  mean_mode_kernel<<<1, kMeanThreads, 0, s>>>(part, level_parts(g), g.nz, (double)g.nxy, g.dz, exact, ctl,
                                      rsub, pb);
 }
 
 void launch_level_mean(const Grid &g, const double *part, int exact, double *gbar, hipStream_t s) {
-  level_mean_kernel<<<1, 256, 0, s>>>(part, level_parts(g), g.nz, (double)g.nxy, exact, gbar);
+  level_mean_kernel<<<1, kMeanThreads, 0, s>>>(part, level_parts(g), g.nz, (double)g.nxy, exact, gbar);
 }
 
 template <typename T>
@@ -742,6 +751,34 @@ void launch_ctl_limit(SolveCtl *ctl, int max_sweeps, hipStream_t s) {
   ctl_limit_kernel<<<1, 64, 0, s>>>(ctl, max_sweeps);
 }
 
+__global__ void ctl_budget_kernel(SolveCtl *ctl, int max_sweeps) {
+  if (threadIdx.x == 0 && ctl->guess_kept) ctl->max_sweeps = max_sweeps;
+}
+
+void launch_ctl_budget(SolveCtl *ctl, int max_sweeps, hipStream_t s) {
+  ctl_budget_kernel<<<1, 64, 0, s>>>(ctl, max_sweeps);
+}
+
+__global__ void ctl_rerun_kernel(SolveCtl *ctl) {
+  if (threadIdx.x != 0) return;
+  ctl->done = 0;
+  ctl->stop_m = -1;
+  ctl->res_norm2 = 0.0;
+  ctl->aborted = 0;
+}
+
+void launch_ctl_rerun(SolveCtl *ctl, hipStream_t s) { ctl_rerun_kernel<<<1, 64, 0, s>>>(ctl); }
+
+__global__ __launch_bounds__(kBlock) void clear_words_kernel(size_t n, uint64_t *__restrict__ w) {
+  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
+       q += (size_t)gridDim.x * blockDim.x)
+    w[q] = 0;
+}
+
+void launch_clear_words(uint64_t *w, size_t n, hipStream_t s) {
+  clear_words_kernel<<<kReduceBlocks, kBlock, 0, s>>>(n, w);
+}
+
 template <typename T>
 void launch_zero(const Grid &g, T *f, hipStream_t s) {
   zero_kernel<T><<<blocks_for(g.n), kBlock, 0, s>>>(g.n, f);
@@ -768,7 +805,13 @@ void launch_extrapolate(const Grid &g, const Profiles<T> &P, const T *p, const T
 // Blocks of the guess/returned-residual kernel: one x row each at a time,
 // enough of them to keep every CU's memory pipes busy; 2 x 4096 partials fit
 // the partial buffer.
-constexpr int kResidualBlocks = 4096;
+// Blocks of guess_residual_kernel: at least its four x rows at a time each
+// (fewer rows are read again for nothing: 64 x 64 x 64 FP32 19.6 us with the
+// most blocks, 8.0 us with 1024), a multiple of 8 for the XCDs.
+constexpr int kResidualBlocks = 4096;  // at most
+inline int residual_blocks(const Grid &g) {
+  return (int)std::min<int64_t>(kResidualBlocks, ((int64_t)g.ny * g.nz + 31) / 32 * 8);
+}
 static_assert(2 * kResidualBlocks <= kPartials, "residual partials exceed the buffer");
 
 // guess_residual_kernel with its GBAR, GV variant picked from gbar, gv.
@@ -778,7 +821,7 @@ void launch_residual_pass(const Grid &g, const T *rhs, const T *phi0, const doub
                           hipStream_t s) {
   const double ix2 = 1.0 / (g.dx * g.dx), iy2 = 1.0 / (g.dy * g.dy), iz2 = 1.0 / (g.dz * g.dz);
 #define LES_RES(GB, GV)                                                            \
-  guess_residual_kernel<T, GB, GV><<<kResidualBlocks, kBlock, 0, s>>>(g, ix2, iy2, iz2, rhs, \
+  guess_residual_kernel<T, GB, GV><<<residual_blocks(g), kBlock, 0, s>>>(g, ix2, iy2, iz2, rhs, \
                                                                       phi0, gbar, gv, rhs_d, \
                                                                       partials, when)
   if (gbar && gv) LES_RES(true, true);
@@ -794,20 +837,28 @@ void launch_guess_gate(const Grid &g, const T *rhs, const T *phi0, const double 
                        int always_keep, hipStream_t s) {
   if (rhs != rhs_d) {
     launch_residual_pass<T>(g, rhs, phi0, gbar, gv, rhs_d, partials, nullptr, s);
-    guess_gate_kernel<<<1, 1024, 0, s>>>(partials, kResidualBlocks, always_keep, ctl);
+    guess_gate_kernel<<<1, 1024, 0, s>>>(partials, residual_blocks(g), always_keep, ctl);
     guess_clear_kernel<T><<<blocks_for(g.n), kBlock, 0, s>>>(g.n, ctl, rhs, rhs_d);
   } else {  // in place: the sums, the gate, then the defect if the guess is kept
     launch_residual_pass<T>(g, rhs, phi0, gbar, gv, nullptr, partials, nullptr, s);
-    guess_gate_kernel<<<1, 1024, 0, s>>>(partials, kResidualBlocks, always_keep, ctl);
+    guess_gate_kernel<<<1, 1024, 0, s>>>(partials, residual_blocks(g), always_keep, ctl);
     launch_residual_pass<T>(g, rhs, phi0, gbar, gv, rhs_d, partials, ctl, s);
   }
+}
+
+template <typename T>
+void launch_guess_defect(const Grid &g, const T *rhs, const T *phi0, const double *gbar,
+                         const double *gv, T *rhs_d, double *partials, SolveCtl *ctl,
+                         int always_keep, hipStream_t s) {
+  launch_residual_pass<T>(g, rhs, phi0, gbar, gv, rhs_d, partials, nullptr, s);
+  guess_gate_kernel<<<1, 1024, 0, s>>>(partials, residual_blocks(g), always_keep, ctl);
 }
 
 template <typename T>
 void launch_returned_residual(const Grid &g, const T *rhs, const T *phi, double *partials,
                               SolveCtl *ctl, hipStream_t s) {
   launch_residual_pass<T>(g, rhs, phi, nullptr, nullptr, nullptr, partials, nullptr, s);
-  final_kernel<<<1, 1024, 0, s>>>(partials, kResidualBlocks, kFinalReturned, ctl, 0.0, 0.0, 0,
+  final_kernel<<<1, 1024, 0, s>>>(partials, residual_blocks(g), kFinalReturned, ctl, 0.0, 0.0, 0,
                                   nullptr);
 }
 
@@ -869,6 +920,9 @@ void launch_ctl_reset(SolveCtl *ctl, int max_sweeps, int fixed, hipStream_t s) {
   template void launch_guess_gate<T>(const Grid &, const T *, const T *, const double *,        \
                                      const double *, T *, double *, SolveCtl *, int,             \
                                      hipStream_t);                                               \
+  template void launch_guess_defect<T>(const Grid &, const T *, const T *, const double *,      \
+                                       const double *, T *, double *, SolveCtl *, int,           \
+                                       hipStream_t);                                             \
   template void launch_add_guess<T>(const Grid &, const T *, const double *, const SolveCtl *,   \
                                     T *, hipStream_t);                                           \
   template void launch_extrapolate<T>(const Grid &, const Profiles<T> &, const T *, const T *,   \

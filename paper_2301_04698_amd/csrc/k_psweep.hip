@@ -1,0 +1,112 @@
+// Which solves run resident on the chip (les_resident.h), and their launch.
+#include "les_resident.h"
+
+namespace lesmi {
+
+using namespace resident;
+
+namespace {
+
+struct Fit {
+  int shape = 0;  // 0 none; 1 S, 2 M, 3 L; 4 RowS, 5 RowL
+  int tx = 0, ty = 0, tz = 0, nb = 0, face = 0;
+  bool rag = false;
+};
+
+// One block per CU: the boxes of shape B, if they all fit at once.
+template <class B>
+bool try_box(const Grid &g, int shape, Fit *f) {
+  const int tx = (g.nx + 63) / 64, ty = (g.ny + B::BY - 1) / B::BY, tz = (g.nz + B::BZ - 1) / B::BZ;
+  if ((int64_t)tx * ty * tz > kResidentBlocks) return false;
+  // one-row boxes: each of the eight waves holds a level
+  if (B::D2 && g.nz / tz < kNW) return false;
+  f->shape = shape;
+  f->tx = tx;
+  f->ty = ty;
+  f->tz = tz;
+  f->nb = tx * ty * tz;
+  f->face = B::FACE;
+  f->rag = g.nx != 64 * tx || g.ny != B::BY * ty || g.nz != B::BZ * tz;
+  return true;
+}
+
+// The smallest shape whose boxes all fit, so that a small grid spreads over
+// many CUs.  Fixed-weight Jacobi sweeps (small grids: their count grows with
+// the square of the grid's width) have no large boxes.
+template <typename T>
+Fit fit_of(const Grid &g, bool chebyshev) {
+  static_assert(kResidentBlocks <= kNT, "every block's partial has a thread that reads it");
+  using S = Shapes<T>;
+  Fit f;
+  if (g.ny == 1) {
+    if (!try_box<typename S::RowS>(g, 4, &f)) try_box<typename S::RowL>(g, 5, &f);
+  } else if (!try_box<typename S::S>(g, 1, &f) && !try_box<typename S::M>(g, 2, &f) && chebyshev) {
+    try_box<typename S::L>(g, 3, &f);
+  }
+  return f;
+}
+
+}  // namespace
+
+template <typename T>
+int psweep_blocks(const Grid &g, bool chebyshev) {
+  return fit_of<T>(g, chebyshev).nb;
+}
+
+template <typename T>
+size_t psweep_words(const Grid &g, bool chebyshev) {
+  const Fit f = fit_of<T>(g, chebyshev);
+  return (size_t)f.nb * (2 * f.face + 4);
+}
+
+template <typename T>
+hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double rho, int every,
+                         uint32_t base, const T *rhs, const T *rhs_kept, T *out, uint64_t *words,
+                         SolveCtl *ctl, hipStream_t s) {
+  const Fit f = fit_of<T>(g, chebyshev);
+  PArgs<T> a;
+  a.g = g;
+  a.k = sweep_coef(g, omega_j);
+  a.w1 = 1.0 / (1.0 - 0.5 * rho * rho);
+  a.q = 0.25 * rho * rho;
+  a.tx = f.tx;
+  a.ty = f.ty;
+  a.tz = f.tz;
+  a.every = every;
+  a.base = base;
+  a.rhs = rhs;
+  a.rhs_kept = rhs_kept;
+  a.out = out;
+  a.faces = words;
+  a.red = words + (size_t)f.nb * 2 * f.face;
+  a.ctl = ctl;
+  using S = Shapes<T>;
+#define LES_BOX(B)                                                            \
+  (chebyshev ? (f.rag ? launch_box<typename S::B, true, true>(a, f.nb, s)     \
+                      : launch_box<typename S::B, true, false>(a, f.nb, s))   \
+             : (f.rag ? launch_box<typename S::B, false, true>(a, f.nb, s)    \
+                      : launch_box<typename S::B, false, false>(a, f.nb, s)))
+  switch (f.shape) {
+    case 1: return LES_BOX(S);
+    case 2: return LES_BOX(M);
+    case 3:
+      return f.rag ? launch_box<typename S::L, true, true>(a, f.nb, s)
+                   : launch_box<typename S::L, true, false>(a, f.nb, s);
+    case 4: return LES_BOX(RowS);
+    case 5: return LES_BOX(RowL);
+    default: return hipErrorInvalidValue;
+  }
+#undef LES_BOX
+}
+
+#define LES_INST(T)                                                                              \
+  template int psweep_blocks<T>(const Grid &, bool);                                             \
+  template size_t psweep_words<T>(const Grid &, bool);                                           \
+  template hipError_t launch_psweep<T>(const Grid &, bool, double, double, int, uint32_t,        \
+                                       const T *, const T *, T *, uint64_t *, SolveCtl *,        \
+                                       hipStream_t);
+LES_INST(float)
+LES_INST(double)
+#undef LES_INST
+
+}  // namespace lesmi

@@ -1,0 +1,11 @@
+// Resident sweep kernels (les_resident.h): FP64, large boxes.
+#include "les_resident.h"
+
+namespace lesmi {
+namespace resident {
+
+LES_RESIDENT(Shapes<double>::L, true, true)
+LES_RESIDENT(Shapes<double>::L, true, false)
+
+}  // namespace resident
+}  // namespace lesmi

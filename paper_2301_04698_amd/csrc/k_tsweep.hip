@@ -2,14 +2,8 @@
 // pressure-correction operator (paper Sec. 2.4 and App. A), one or two
 // sweeps per launch.
 //
-// Point update, shared by every kernel so their results are bitwise equal:
-//   r   = rhs - (N(phi) - D phi)     N: off-diagonal neighbour sum, FP64
-//   J   = phi - omega_j r / D         (weighted Jacobi)
-//   out = J, or Chebyshev: prev + omega_c (J - prev)
-// formed in FP64 from the stored values with explicit FMAs (no other
-// contraction) and rounded once to the storage type.  An FP32 update
-// written as (N - rhs)/D - phi cancels catastrophically; its rounding error
-// is the same from sweep to sweep and accumulates in the slow modes.
+// The point update is les_sweep.h's, so the iterates of every kernel are
+// bitwise equal.
 //
 // One sweep: each thread owns one column of the tile and marches up z
 // with the vertical neighbours in registers; x neighbours come from the
@@ -30,28 +24,11 @@
 // Walls: the z neighbour of the bottom/top level is that level itself (even
 // mirror); x and y are periodic.
 #include "les_column.h"
+#include "les_sweep.h"
 
 namespace lesmi {
 
 namespace {
-
-struct SweepCoef {
-  double ix2, iy2, iz2, diag, inv_diag, omega_j;
-};
-
-__device__ __forceinline__ double point_residual(const SweepCoef &k, double c0, double hx,
-                                                 double hy, double hz, double rhs) {
-#pragma clang fp contract(off)
-  const double lap = fma(hx, k.ix2, fma(hy, k.iy2, fma(hz, k.iz2, -k.diag * c0)));
-  return rhs - lap;
-}
-
-__device__ __forceinline__ double point_update(const SweepCoef &k, double c0, double res,
-                                               bool cheb, double pv, double wc) {
-#pragma clang fp contract(off)
-  const double jac = fma(-k.omega_j * k.inv_diag, res, c0);
-  return cheb ? fma(wc, jac - pv, pv) : jac;
-}
 
 __device__ __forceinline__ int pmod(int i, int n) {
   int r = i % n;
@@ -115,22 +92,6 @@ constexpr int kWideNx = 256, kWX = 4, kWideTY = 2, kWideTYBig = 4;
 template <typename T>
 __device__ __forceinline__ T ld_stream(const T *p, bool nt) {
   return nt ? __builtin_nontemporal_load(p) : *p;
-}
-
-// Value of v in the next (+1) or previous (-1) lane of the 64-wide
-// wavefront by DPP wave shifts; a lane without a source keeps its own value
-// (the caller replaces the end lanes).  A double moves as two 32-bit halves.
-template <int DIR>
-__device__ __forceinline__ float lane_shift(float v) {
-  const int x = __float_as_int(v);
-  return __int_as_float(__builtin_amdgcn_update_dpp(x, x, DIR > 0 ? 0x130 : 0x138, 0xF, 0xF, false));
-}
-template <int DIR>
-__device__ __forceinline__ double lane_shift(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  const int ctrl = DIR > 0 ? 0x130 : 0x138;
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, ctrl, 0xF, 0xF, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, ctrl, 0xF, 0xF, false));
 }
 
 // z-march of one 64-cell row (one wave) of a tile over levels [k0, k1):
@@ -493,12 +454,7 @@ void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
   const Shape sh = shape_of(g, S, sizeof(T) == 8);
   SweepArgs<T> a;
   a.g = g;
-  a.k.ix2 = 1.0 / (g.dx * g.dx);
-  a.k.iy2 = 1.0 / (g.dy * g.dy);
-  a.k.iz2 = 1.0 / (g.dz * g.dz);
-  a.k.diag = 2.0 * (a.k.ix2 + a.k.iy2 + a.k.iz2);
-  a.k.inv_diag = 1.0 / a.k.diag;
-  a.k.omega_j = omega_jacobi;
+  a.k = sweep_coef(g, omega_jacobi);
   a.kc = sh.kc;
   a.tiles_x = sh.tiles_x;
   a.tiles_y = sh.tiles_y;

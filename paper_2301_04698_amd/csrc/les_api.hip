@@ -58,6 +58,7 @@ struct Layout {
   // learned guess: residual (FP32), network input (bf16), two 16-channel
   // activations (bf16), parameters (FP32) and their bf16 copy, scales
   size_t cnn_r, cnn_a0, cnn_act[2], cnn_params, cnn_packed, cnn_sc;
+  size_t words, n_words;  // exchange words of the resident solves (0: the grid does not fit)
   size_t total;
 };
 
@@ -135,6 +136,30 @@ int cnn_inputs_of(const les_config *c) {
   return c->guess == LES_GUESS_LEARNED ? 1 : c->guess == LES_GUESS_LEARNED3 ? 3 : 0;
 }
 
+Grid grid_of(const les_config *c) {
+  Grid g;
+  g.nx = c->nx;
+  g.ny = c->ny;
+  g.nz = c->nz;
+  g.nxy = (int64_t)c->nx * c->ny;
+  g.sy = c->ny == 1 ? 0 : c->nx;
+  g.n = g.nxy * c->nz;
+  g.dx = c->dx;
+  g.dy = c->dy;
+  g.dz = c->dz;
+  g.dt = c->dt;
+  return g;
+}
+
+// Exchange words of the resident solves of a configuration: 0 where the grid
+// does not fit the chip, and where the caller chose the sweeps per launch.
+size_t resident_words(const les_config *c) {
+  if (c->sweeps_per_launch > 0) return 0;
+  const Grid g = grid_of(c);
+  const bool cheb = c->poisson_scheme == LES_CHEBYSHEV;
+  return c->precision == LES_FP64 ? psweep_words<double>(g, cheb) : psweep_words<float>(g, cheb);
+}
+
 Layout layout_of(const les_config *c) {
   Layout L;
   const size_t n = (size_t)c->nx * c->ny * c->nz;
@@ -182,6 +207,9 @@ Layout layout_of(const les_config *c) {
   if (cnn) off = align_up(off + (size_t)cnn_param_count(ci) * sizeof(uint16_t));
   L.cnn_sc = off;
   if (cnn) off = align_up(off + 4 * sizeof(double));
+  L.words = off;
+  L.n_words = resident_words(c);
+  off = align_up(off + L.n_words * sizeof(uint64_t));
   L.total = off;
   return L;
 }
@@ -210,6 +238,8 @@ struct les_handle {
                                      // zero start (a kept guess's budget; 0 none yet)
   bool cnn_bound;                // learned guess: parameters bound
   float cnn_alpha;               // its leaky ReLU slope
+  bool resident;                 // solves run resident on the chip where their cap allows
+  uint32_t tag;                  // first unused tag of the resident solves' exchange words
   int64_t steps_done;            // time steps taken since les_init (or the imported count)
 };
 
@@ -256,6 +286,7 @@ struct View {
   T *pgz_w, *cbar_w, *phigz_w;  // writable views of the profile terms
   int exact;                    // the horizontally uniform part solved exactly
   int vert;                     // the vertically uniform part too (LES_MEAN_EXACT)
+  bool res;                     // this solve's sweeps run resident on the chip
 };
 
 template <typename T>
@@ -393,6 +424,39 @@ struct SweepTiming {
   int64_t sweeps = 0;
 };
 
+// Weight of the Jacobi step and, for the Chebyshev recurrence, the half-width
+// of the spectrum over its centre.
+struct SweepWeights {
+  double omega_j, rho;
+};
+SweepWeights sweep_weights(const les_handle *h) {
+  const les_config &c = h->cfg;
+  const double gamma = 2.0 / (h->mu_min + h->mu_max);
+  const bool given = c.poisson_scheme != LES_CHEBYSHEV && c.jacobi_omega > 0;
+  return SweepWeights{given ? c.jacobi_omega : gamma,
+                      (h->mu_max - h->mu_min) / (h->mu_max + h->mu_min)};
+}
+
+// A resident solve's blocks wait for each other, so all of them have to be
+// on the GPU at once: a cooperative launch of at most one block per CU.
+bool resident_fits(const les_handle *h) {
+  if (h->lay.n_words == 0) return false;
+  const bool cheb = h->cfg.poisson_scheme == LES_CHEBYSHEV;
+  const int nb = h->cfg.precision == LES_FP64 ? psweep_blocks<double>(h->grid, cheb)
+                                              : psweep_blocks<float>(h->grid, cheb);
+  int dev = 0, coop = 0, cus = 0;
+  const bool ok =
+      hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+  return ok && coop && nb > 0 && nb <= cus;
+}
+
+// Sweep caps above this run launch by launch: one resident launch does all
+// the sweeps of a solve, and a solve that never converges should not hold
+// the GPU for longer than some seconds.
+constexpr int kResidentMaxSweeps = 1 << 20;
+
 // Centred right-hand side of a solve into F_RHS (rhs_in may be F_RHS
 // itself): the mean removed and, with the horizontally uniform part solved
 // exactly, the horizontal mean of every level, whose part of the solution
@@ -407,6 +471,7 @@ int prepare_rhs(les_handle *h, View<T> &V, const T *rhs_in, int max_sweeps, bool
   const Grid &g = h->grid;
   hipStream_t s = h->stream;
   const double tol = h->cfg.poisson_tol;
+  V.res = h->resident && max_sweeps <= kResidentMaxSweeps;
   launch_ctl_reset(V.ctl, max_sweeps, fixed ? 1 : 0, s);
   launch_level_sum<T>(g, rhs_in, V.lvl_part, s);
   launch_mean_mode(g, V.lvl_part, V.exact, V.ctl, V.rsub, V.phibar, s);
@@ -435,6 +500,9 @@ T *sweep_rhs(View<T> &V) {
 // of V.phibar), gv its column means when those are (already part of V.pv).
 // The guess is kept if always_keep or its residual is below the zero
 // start's; a dropped guess leaves F_RHSD the zero start's right-hand side.
+// Resident solves (V.res) take the defect from F_PHI1, which they do not use
+// otherwise, and choose by the gate themselves: the defect is then formed in
+// one pass with the sums that the gate needs.
 template <typename T>
 int prepare_guess(les_handle *h, View<T> &V, const T *guess, bool always_keep) {
   const Grid &g = h->grid;
@@ -442,11 +510,40 @@ int prepare_guess(les_handle *h, View<T> &V, const T *guess, bool always_keep) {
   launch_level_sum<T>(g, guess, V.lvl_part, s);
   launch_level_mean(g, V.lvl_part, V.exact, V.gbar, s);
   if (V.vert) launch_column_mean<T>(g, guess, V.gv, s);
-  launch_guess_gate<T>(g, sweep_rhs(V), guess, V.exact ? V.gbar : nullptr,
-                       V.vert ? V.gv : nullptr, V.f[F_RHSD], V.partials, V.ctl,
-                       always_keep ? 1 : 0, s);
+  if (V.res)
+    launch_guess_defect<T>(g, sweep_rhs(V), guess, V.exact ? V.gbar : nullptr,
+                           V.vert ? V.gv : nullptr, V.f[F_PHI1], V.partials, V.ctl,
+                           always_keep ? 1 : 0, s);
+  else
+    launch_guess_gate<T>(g, sweep_rhs(V), guess, V.exact ? V.gbar : nullptr,
+                         V.vert ? V.gv : nullptr, V.f[F_RHSD], V.partials, V.ctl,
+                         always_keep ? 1 : 0, s);
   LAUNCH_TRY();
   return LES_OK;
+}
+
+// The sweeps of a solve (run_sweeps) as one resident launch, queued: rhs, or
+// rhs_kept (nullable) if the guess was kept, phi into F_PHI0.  False if the
+// launch was refused: nothing ran, and the handle launches none any more.
+template <typename T>
+bool launch_resident(les_handle *h, View<T> &V, const T *rhs, const T *rhs_kept, int max_sweeps) {
+  hipStream_t s = h->stream;
+  const les_config &c = h->cfg;
+  uint64_t *words = (uint64_t *)ws(h, h->lay.words);
+  const SweepWeights w = sweep_weights(h);
+  const uint32_t span = (uint32_t)max_sweeps + 4;
+  if (h->tag > UINT32_MAX - span) {  // tags used up: start over on cleared words
+    launch_clear_words(words, h->lay.n_words, s);
+    h->tag = 1;
+  }
+  if (launch_psweep<T>(h->grid, c.poisson_scheme == LES_CHEBYSHEV, w.omega_j, w.rho,
+                       c.poisson_check_every, h->tag, rhs, rhs_kept, V.f[F_PHI0], words, V.ctl,
+                       s) != hipSuccess) {
+    (void)hipGetLastError();
+    h->resident = false;
+    return false;
+  }
+  return true;
 }
 
 // Sweeps on L phi = rhs from zero until the device-side residual test
@@ -463,11 +560,8 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
   const int max_sweeps = fixed > 0 ? fixed : (cap > 0 ? cap : c.poisson_max_sweeps);
   const int every = c.poisson_check_every;
   const bool cheb = c.poisson_scheme == LES_CHEBYSHEV;
-  const double gamma = 2.0 / (h->mu_min + h->mu_max);
-  const double rho = (h->mu_max - h->mu_min) / (h->mu_max + h->mu_min);
-  const double omega_j = cheb ? gamma : (c.jacobi_omega > 0 ? c.jacobi_omega : gamma);
+  const auto [omega_j, rho] = sweep_weights(h);
   const int smax = h->sweeps_per_launch;
-
   // Launches of up to smax sweeps, made one at a time; a residual check at
   // sweep m is computed by the launch that starts at m (its input iterate
   // is phi_m), so launches are cut at check positions.  Checks at every
@@ -689,57 +783,108 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
   hipStream_t s = h->stream;
   SolveCtl r;
   T *phi = nullptr;
+  double res2 = 0.0;
+  // a kept guess's budget, as the cap of its sweeps (0: none)
   int cap = 0;
   if (guess && gated && fixed == 0 && budget > 0) {
-    // a kept guess gets the budget (the gate's decision is read back first,
-    // so a dropped guess's zero start keeps the whole cap)
-    HIP_TRY(hipMemcpyAsync(&h->ctl_host[0], V.ctl, sizeof(SolveCtl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
     const int every = c.poisson_check_every;
     const int64_t b = ((int64_t)budget + every - 1) / every * every;
-    if (h->ctl_host[0].guess_kept && b < c.poisson_max_sweeps) {
-      cap = (int)b;
-      launch_ctl_limit(V.ctl, cap, s);
-      LAUNCH_TRY();
-    }
+    if (b < c.poisson_max_sweeps) cap = (int)b;
   }
-  // With the vertically uniform part exact, every returned iterate is
-  // assembled (the correction projected, plus pv and the guess) and its
-  // residual taken against F_RHS.
-  auto assemble = [&](T *x, const T *gs) -> int {
-    launch_level_sum<T>(g, x, V.lvl_part, s);
-    launch_level_mean(g, V.lvl_part, 1, V.dbar, s);
-    launch_column_mean<T>(g, x, V.dv, s);
-    launch_combine<T>(g, x, V.dbar, V.dv, V.pv, gs, V.gbar, V.gv, V.ctl, s);
+  // The returned iterate from the sweeps' x and guess gs, queued: with the
+  // vertically uniform part exact every one is assembled (the correction
+  // projected, plus pv and the guess), otherwise a kept guess is added; then
+  // its residual against F_RHS.
+  auto assemble = [&](T *x, const T *gs) {
+    if (V.vert) {
+      launch_level_sum<T>(g, x, V.lvl_part, s);
+      launch_level_mean(g, V.lvl_part, 1, V.dbar, s);
+      launch_column_mean<T>(g, x, V.dv, s);
+      launch_combine<T>(g, x, V.dbar, V.dv, V.pv, gs, V.gbar, V.gv, V.ctl, s);
+    } else {
+      launch_add_guess<T>(g, gs, V.exact ? V.gbar : nullptr, V.ctl, x, s);
+    }
     launch_returned_residual<T>(g, V.f[F_RHS], x, V.partials, V.ctl, s);
+  };
+  // Reads the control block back once everything queued has run; ev_s1 ends
+  // the solve's time here.
+  auto read_ctl = [&]() -> int {
     LAUNCH_TRY();
+    HIP_TRY(hipEventRecord(h->ev_s1, s));
     HIP_TRY(hipMemcpyAsync(&h->ctl_host[0], V.ctl, sizeof(SolveCtl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    r = h->ctl_host[0];
     return LES_OK;
   };
-  int rc = run_sweeps<T>(h, V, guess ? V.f[F_RHSD] : sweep_rhs(V), fixed, cap, &r, &phi, timing);
+  // One pass of sweeps from zero, to the returned iterate phi, its residual
+  // res2 and the control block r as it ended: on the guess's defect if gs was
+  // given and kept, else on the zero start's right-hand side.  sweep_cap: cap
+  // of a kept guess's sweeps (0: the configuration's).
+  auto pass = [&](const T *gs, int sweep_cap) -> int {
+    const int most = fixed > 0 ? fixed : c.poisson_max_sweeps;
+    const bool was_resident = V.res;
+    if (V.res) {
+      // Everything is queued before the one read-back: the gate's outcome is
+      // taken on the device.
+      const bool timed = timing && timing->enabled;
+      while (timed && h->ev_sweep.size() < 2) {
+        hipEvent_t ev;
+        HIP_TRY(hipEventCreate(&ev));
+        h->ev_sweep.push_back(ev);
+      }
+      if (gs && sweep_cap > 0) launch_ctl_budget(V.ctl, sweep_cap, s);
+      if (timed) HIP_TRY(hipEventRecord(h->ev_sweep[0], s));
+      V.res = launch_resident<T>(h, V, sweep_rhs(V), gs ? V.f[F_PHI1] : nullptr, most);
+      if (V.res) {
+        if (timed) HIP_TRY(hipEventRecord(h->ev_sweep[1], s));
+        phi = V.f[F_PHI0];
+        if (V.vert || gs) assemble(phi, gs);
+        if (int rc = read_ctl()) return rc;
+        if (!r.aborted) {
+          if (r.done == 0 || r.stop_m < 0)
+            return fail(LES_ERR_STATE, "Poisson solve ended without a decision");
+          h->tag += (uint32_t)r.stop_m + 2;
+          if (timed && r.stop_m > 0) {
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, h->ev_sweep[0], h->ev_sweep[1]));
+            timing->seconds += ms * 1e-3;
+            timing->sweeps += r.stop_m + 1;
+          }
+          if (r.done == 2) return fail(LES_ERR_NONFINITE, "non-finite Poisson residual");
+          res2 = V.vert || (gs && r.guess_kept) ? r.res_out2 : r.res_norm2;
+          return LES_OK;
+        }
+        h->resident = V.res = false;
+        launch_ctl_rerun(V.ctl, s);
+        launch_zero<T>(g, V.f[F_PHI0], s);
+      }
+    }
+    const T *rhs = sweep_rhs(V);
+    if (gs) {  // the gate's outcome
+      if (int rc = read_ctl()) return rc;
+      if (!was_resident || r.guess_kept) rhs = V.f[F_RHSD];
+      if (was_resident && r.guess_kept)  // the sweeps below use F_PHI1
+        HIP_TRY(hipMemcpyAsync(V.f[F_RHSD], V.f[F_PHI1], (size_t)g.n * sizeof(T),
+                               hipMemcpyDeviceToDevice, s));
+    }
+    // a dropped guess's zero start keeps the whole cap
+    const int rcap = gs && r.guess_kept ? sweep_cap : 0;
+    if (rcap > 0 && !was_resident) launch_ctl_limit(V.ctl, rcap, s);
+    if (int rc = run_sweeps<T>(h, V, rhs, fixed, rcap, &r, &phi, timing))
+      return rc;
+    res2 = r.res_norm2;
+    if (V.vert || (gs && r.guess_kept)) {
+      assemble(phi, gs);
+      if (int rc = read_ctl()) return rc;
+      res2 = r.res_out2;
+    }
+    return LES_OK;
+  };
+  int rc = pass(guess, cap);
   if (rc) return rc;
   int sweeps = r.stop_m, first = 0;
   int flag = guess ? (r.guess_kept ? 1 : 2) : 0;
-  double res2 = r.res_norm2;
-  // the returned iterate from the sweeps' phi and guess gs: its FP64
-  // residual into res2 (r the control block as it ended)
-  auto finish = [&](const T *gs) -> int {
-    if (V.vert) {
-      if ((rc = assemble(phi, gs))) return rc;
-    } else {
-      launch_add_guess<T>(g, gs, V.exact ? V.gbar : nullptr, V.ctl, phi, s);
-      launch_returned_residual<T>(g, V.f[F_RHS], phi, V.partials, V.ctl, s);
-      LAUNCH_TRY();
-      HIP_TRY(hipMemcpyAsync(&h->ctl_host[0], V.ctl, sizeof(SolveCtl), hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
-    }
-    r = h->ctl_host[0];
-    res2 = r.res_out2;
-    return LES_OK;
-  };
   if (V.vert || (guess && r.guess_kept)) {
-    if ((rc = finish(guess))) return rc;
     bool missed = r.done == 3 || !(res2 <= r.tol2);
     if (guess && r.guess_kept && gated && fixed == 0 && missed && r.done == 1) {
       // The sweeps met the test but the returned iterate (guess plus
@@ -761,14 +906,10 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
       if (V.vert) launch_remove_columns<T>(g, V.f[F_RHS], V.cmean, V.ctl, V.f[F_RHSD], s);
       LAUNCH_TRY();
       if ((rc = prepare_guess<T>(h, V, V.f[F_GUESS], true))) return rc;
-      launch_ctl_limit(V.ctl, ccap, s);
-      LAUNCH_TRY();
-      rc = run_sweeps<T>(h, V, V.f[F_RHSD], 0, ccap, &r, &phi, timing);
-      if (rc) return rc;
+      if ((rc = pass(V.f[F_GUESS], ccap))) return rc;
       first = sweeps;
       sweeps += r.stop_m;
       flag = 4;
-      if ((rc = finish(V.f[F_GUESS]))) return rc;
       missed = r.done == 3 || !(res2 <= r.tol2);
     }
     if (guess && r.guess_kept && gated && fixed == 0 && missed) {
@@ -777,24 +918,20 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
       // the zero start's right-hand side again (the defect overwrote it)
       if (V.vert) launch_remove_columns<T>(g, V.f[F_RHS], V.cmean, V.ctl, V.f[F_RHSD], s);
       LAUNCH_TRY();
-      rc = run_sweeps<T>(h, V, sweep_rhs(V), 0, 0, &r, &phi, timing);
-      if (rc) return rc;
+      if ((rc = pass(nullptr, 0))) return rc;  // guess_kept is 0 now
       first = sweeps;
       sweeps += r.stop_m;
-      res2 = r.res_norm2;
       flag = 3;
-      if (V.vert) {  // guess_kept is 0 now: pv and the projected correction
-        if ((rc = assemble(phi, guess))) return rc;
-        r = h->ctl_host[0];
-        res2 = r.res_out2;
-        if (r.done == 1 && !(res2 <= r.tol2)) r.done = 3;
-      }
+      if (V.vert && r.done == 1 && !(res2 <= r.tol2)) r.done = 3;
     } else if (r.done == 1 && !(res2 <= r.tol2)) {
       r.done = 3;  // the returned iterate misses the tolerance
     }
   }
-  HIP_TRY(hipEventRecord(h->ev_s1, s));
-  HIP_TRY(hipEventSynchronize(h->ev_s1));
+  if (!V.vert && !(guess && flag != 0 && flag != 3 && r.guess_kept)) {
+    // nothing followed the sweeps, which ended synchronized
+    HIP_TRY(hipEventRecord(h->ev_s1, s));
+    HIP_TRY(hipEventSynchronize(h->ev_s1));
+  }
   float ms = 0.f;
   HIP_TRY(hipEventElapsedTime(&ms, h->ev_s0, h->ev_s1));
   st->sweeps = sweeps;
@@ -1274,17 +1411,8 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->stream = (hipStream_t)stream;
   h->lay = L;
   h->broken = false;
-  Grid &g = h->grid;
-  g.nx = cfg->nx;
-  g.ny = cfg->ny;
-  g.nz = cfg->nz;
-  g.nxy = (int64_t)cfg->nx * cfg->ny;
-  g.sy = cfg->ny == 1 ? 0 : cfg->nx;
-  g.n = g.nxy * cfg->nz;
-  g.dx = cfg->dx;
-  g.dy = cfg->dy;
-  g.dz = cfg->dz;
-  g.dt = cfg->dt;
+  h->grid = grid_of(cfg);
+  const Grid &g = h->grid;
   Thermo &t = h->thermo;
   t.p00 = cfg->p00;
   t.Rd = cfg->Rd;
@@ -1313,6 +1441,8 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->cnn_bound = false;
   h->cnn_alpha = 0.f;
   h->steps_done = 0;
+  h->resident = resident_fits(h);
+  h->tag = 1;
   h->sweeps_per_launch = cfg->sweeps_per_launch > 0 ? cfg->sweeps_per_launch : kDefaultSweepsPerLaunch;
 
   auto cleanup = [&](int code) {
@@ -1339,6 +1469,8 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   if (!rc && hipMemcpyAsync(ws(h, L.field[F_PM2]), bufs->p, (size_t)g.n * es,
                             hipMemcpyDeviceToDevice, h->stream) != hipSuccess)
     rc = fail(LES_ERR_HIP, "copy of the initial pressure failed");
+  if (!rc && h->resident)
+    launch_clear_words((uint64_t *)ws(h, L.words), L.n_words, h->stream);
   if (!rc && hipStreamSynchronize(h->stream) != hipSuccess)
     rc = fail(LES_ERR_HIP, "hipStreamSynchronize failed");
   if (rc) return cleanup(rc);

@@ -70,7 +70,7 @@ struct SolveCtl {
   int32_t max_sweeps;
   int32_t fixed;      // 1: stop at max_sweeps whatever the residual
   int32_t guess_kept; // starting-iterate test (not reset by a solve): 1 kept
-  int32_t pad;
+  int32_t aborted;    // a resident solve gave up a wait (its result is not valid)
   double res_out2;    // residual^2 of a guessed solve's returned iterate
 };
 
@@ -177,6 +177,8 @@ void launch_rhs_center(const Grid &g, const T *rhs_in, T *rhs_out, T *phi0, cons
 void launch_ctl_restart(SolveCtl *ctl, int max_sweeps, hipStream_t s);
 // ctl->max_sweeps = max_sweeps (a kept guess's budget).
 void launch_ctl_limit(SolveCtl *ctl, int max_sweeps, hipStream_t s);
+// ctl->max_sweeps = max_sweeps if ctl->guess_kept.
+void launch_ctl_budget(SolveCtl *ctl, int max_sweeps, hipStream_t s);
 // f = 0 (a fill kernel rather than a memset, so the call records no memset
 // node when a caller captures the stream into a graph).
 template <typename T>
@@ -195,6 +197,31 @@ void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
                    T *out_last, T *out_prev, const T *rhs, SolveCtl *ctl, double *partials,
                    const double *dec_partials, int dec_np, int dec_m, int64_t *snap,
                    int snap_seq, hipStream_t s);
+
+// Whole solves resident on the chip (les_resident.h).  psweep_blocks: blocks
+// of such a launch, 0 where the grid does not fit; at most kResidentBlocks,
+// one per CU, all resident at once (a cooperative launch).  psweep_words:
+// 64-bit words of its exchange buffer.  launch_psweep: the sweeps of
+// L phi = rhs from zero, stopping test included, by ctl as launch_ctl_reset
+// and the rhs norm set it (every: sweeps between tests); on return of the
+// stream ctl holds the outcome and out, which is zero before, phi.  With
+// rhs_kept (nullable) the right-hand side is that if ctl->guess_kept.  base:
+// iterates are tagged base .. base + sweeps + 1, none of them used on this
+// buffer since it was cleared.  ctl->aborted: a wait was given up and the
+// result is not valid.
+constexpr int kResidentBlocks = 256;
+template <typename T>
+int psweep_blocks(const Grid &g, bool chebyshev);
+template <typename T>
+size_t psweep_words(const Grid &g, bool chebyshev);
+template <typename T>
+hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double rho, int every,
+                         uint32_t base, const T *rhs, const T *rhs_kept, T *out, uint64_t *words,
+                         SolveCtl *ctl, hipStream_t s);
+// w[0 .. n) = 0.
+void launch_clear_words(uint64_t *w, size_t n, hipStream_t s);
+// The sweeps start over after an aborted resident solve: ctl as before it.
+void launch_ctl_rerun(SolveCtl *ctl, hipStream_t s);
 
 template <typename T>
 void launch_project(const Grid &g, const Dyn<T> &d, const Profiles<T> &P, const T *phi,
@@ -218,6 +245,12 @@ template <typename T>
 void launch_guess_gate(const Grid &g, const T *rhs, const T *phi0, const double *gbar,
                        const double *gv, T *rhs_d, double *partials, SolveCtl *ctl,
                        int always_keep, hipStream_t s);
+// The same in one pass, rhs_d another field than rhs: where the guess is
+// dropped (ctl->guess_kept 0) rhs_d is not to be used.
+template <typename T>
+void launch_guess_defect(const Grid &g, const T *rhs, const T *phi0, const double *gbar,
+                         const double *gv, T *rhs_d, double *partials, SolveCtl *ctl,
+                         int always_keep, hipStream_t s);
 // phi += phi0 - gbar (FP64 sum, rounded once) when ctl->guess_kept.
 template <typename T>
 void launch_add_guess(const Grid &g, const T *phi0, const double *gbar, const SolveCtl *ctl,
