@@ -47,7 +47,7 @@ struct CnnGeom {
 CnnGeom cnn_geom(int batch, int nz, int ny, int nx, int periodic, int layer, int inputs);
 
 // Weight-gradient reduction: blocks of one launch (their partials).
-constexpr int kCnnWgradBlocks = 1024;
+constexpr int kCnnWgradBlocks = 256;
 
 // ------------------------------------------------------------ launchers
 // wbf[q] = bf16(params[q]), q < n.

@@ -39,6 +39,7 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
@@ -133,12 +134,27 @@ constexpr int kCnnPairs = 5;
 // contiguous reads, while a 48-B stride costs 1.8x.
 constexpr int kCnnCellB = 32;
 
-// Tiles of a launch: 64 x 4 in the plane, chunks of `levels` z levels.  A
-// chunk costs its levels and two planes more, so the longest (16) does the
-// least work; but a grid of few tiles then leaves CUs idle while each block
-// walks its 18 planes.  Two blocks share a CU, so the time goes as the
-// rounds of 512 blocks that the launch takes times the planes of a block;
-// the chunk length with the least of that is taken, the longest on a tie.
+// Levels of a z chunk, at most `longest`.  A chunk costs its levels and two
+// planes more, so the longest does the least work; but a launch of few tiles
+// then leaves CUs idle while each chunk walks its planes.  `slots` chunks run
+// at a time, so the time goes as the rounds of that many that the launch
+// takes times the planes of a chunk; the length with the least of that is
+// taken, the longest on a tie.
+inline int chunk_levels(int64_t tiles, int nz, int longest, int slots) {
+  int64_t best = INT64_MAX;
+  int levels = longest;
+  for (int kc = longest; kc >= 2; --kc) {
+    const int64_t rounds = (tiles * ((nz + kc - 1) / kc) + slots - 1) / slots;
+    if (rounds * (kc + 2) < best) {
+      best = rounds * (kc + 2);
+      levels = kc;
+    }
+  }
+  return levels;
+}
+
+// Tiles of a launch: 64 x 4 in the plane, chunks of `levels` z levels, two
+// blocks on a CU.
 // One 64 x 64 x 64 field (64 blocks at 16 levels, 512 at 2): layers 0 + 1,
 // 2, 3 take 45, 24, 21 us at 16 levels and 19, 11, 9 us at 2.
 // A level's sums run over its three planes in the same order whatever the
@@ -150,17 +166,8 @@ inline CnnTiling cnn_tiling(const CnnGeom &G) {
   CnnTiling C;
   C.tiles_x = (G.nxo + kCnnTX - 1) / kCnnTX;
   C.tiles_y = (G.nyo + kCnnTY - 1) / kCnnTY;
-  int64_t best = INT64_MAX;
-  for (int kc = kCnnKC; kc >= 2; --kc) {
-    const int chunks = (G.nz + kc - 1) / kc;
-    const int64_t blocks = (int64_t)G.batch * C.tiles_x * C.tiles_y * chunks;
-    const int64_t cost = (blocks + 511) / 512 * (kc + 2);
-    if (cost < best) {
-      best = cost;
-      C.chunks = chunks;
-      C.levels = kc;
-    }
-  }
+  C.levels = chunk_levels((int64_t)G.batch * C.tiles_x * C.tiles_y, G.nz, kCnnKC, 512);
+  C.chunks = (G.nz + C.levels - 1) / C.levels;
   return C;
 }
 inline unsigned cnn_blocks(const CnnGeom &G, const CnnTiling &C) {
@@ -219,6 +226,12 @@ __device__ __forceinline__ int64_t cnn_src(const CnnGeom &G, const CnnTile &T, i
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+__device__ __forceinline__ floatx4 mfma32f(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ doublex4 mfma64(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
 __device__ __forceinline__ floatx4 mfma32(bf16x8 a, bf16x8 b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -817,20 +830,168 @@ __global__ __launch_bounds__(kBlock) void loss_b_kernel(int64_t n, int nz, int n
 // src(out cell, tap) = cell' of gy(out cell, o) W[tap][o][i].  The z mirror
 // makes wall cells receive a second term: out level 0 at dz = -1 reads
 // level 0, out level nz-1 at dz = +1 reads level nz-1.
-template <int CI, int CO>
-__global__ __launch_bounds__(kBlock) void dgrad_kernel(CnnGeom G, const float *__restrict__ gy,
-                                                       const uint16_t *__restrict__ wl,
-                                                       const uint16_t *__restrict__ ain,
-                                                       float alpha, float *__restrict__ gprev) {
-  __shared__ float w[kCnnTaps * CO * CI];
-  for (int e = threadIdx.x; e < kCnnTaps * CO * CI; e += blockDim.x) w[e] = bf2f(wl[e]);
+// Layers 1, 2 (16 -> 16) on the matrix cores in FP32 (v_mfma_f32_16x16x4,
+// sums FP32): D(channel i, cell) += W(i, o) g(o, cell) over the 27 taps.  A
+// wave takes two chains of 16 cells of a plane (consecutive in its y-x order,
+// so that ragged planes waste nothing) and marches the gradient's planes p =
+// k0 - 1 .. k1 of its z chunk: plane p feeds levels p - 1, p, p + 1 through
+// the tap rows dz = -1, 0, +1, so that each gradient value is read once per
+// in-plane tap (16 B per lane: channels 4 (l / 16) + 0..3 of cell l % 16, the
+// reduction's order matching on both sides) and serves three products.  The
+// weights stay in registers.  Levels 0 and nz - 1 also take the product that
+// their mirror image read.
+// Bound by the FP32 matrix rate (125 to 130 TFLOP/s measured).  16 crops of
+// 42 x 42 x 128, layers 1 and 2 together: 2.63 ms with a thread per cell on
+// the vector units, 0.88 ms here.
+constexpr int kDgradChains = 2, kDgradLevels = 32;
+
+__global__ __launch_bounds__(256, 2) void dgrad_mid_kernel(CnnGeom G, const float *__restrict__ gy,
+                                                           const uint16_t *__restrict__ wl,
+                                                           const uint16_t *__restrict__ ain,
+                                                           float alpha, float *__restrict__ gprev,
+                                                           int tasks, int levels, int chunks) {
+  constexpr int C = kCnnCh, NC = kDgradChains;
+  const int lane = threadIdx.x & 63, row = lane & 15, quad = lane >> 4;
+  // tasks per plane, then z chunks, then batch items; XCD x takes the x-th
+  // contiguous part of the blocks
+  const int per = (int)(gridDim.x >> 3);
+  const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  int id = __builtin_amdgcn_readfirstlane(blk * 4 + (int)(threadIdx.x >> 6));
+  if (id >= tasks * chunks * G.batch) return;
+  const int task = id % tasks;
+  id /= tasks;
+  const int k0 = id % chunks * levels, b = id / chunks, k1 = min(G.nz, k0 + levels);
+  const int plane_in = G.nyi * G.nxi, plane_out = G.nyo * G.nxo;
+
+  float w[kCnnTaps][4];
+#pragma unroll
+  for (int t = 0; t < kCnnTaps; ++t)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) w[t][m] = bf2f(wl[(t * C + 4 * quad + m) * C + row]);
+
+  // per chain: the lane's cell, its gradient offset in a plane at the tap (0,
+  // 0) and which of the nine taps stay inside the plane
+  int cell[NC], off[NC];
+  uint32_t ok[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    cell[c] = (task * NC + c) * 16 + row;
+    const int cc = min(cell[c], plane_in - 1), j = cc / G.nxi, i = cc - j * G.nxi;
+    off[c] = (j - 1) * G.nxo + i - 1;
+    ok[c] = 0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int jo = j - 1 - (t / 3 - 1), io = i - 1 - (t % 3 - 1);
+      if (jo >= 0 && jo < G.nyo && io >= 0 && io < G.nxo) ok[c] |= 1u << t;
+    }
+  }
+  // the gradient of one row of taps of plane p, read a row ahead of its use
+  // (taps outside the plane read its first cell and count as zero)
+  struct Row {
+    floatx4 g[3][NC];
+  };
+  auto load = [&](int p, auto yc, Row &d) __attribute__((always_inline)) {
+    constexpr int y = decltype(yc)::value;
+    const float *gp = gy + ((int64_t)b * G.nz + min(p, G.nz - 1)) * plane_out * C + 4 * quad;
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const bool in = (ok[c] >> (3 * y + x)) & 1u;
+        const int o = in ? off[c] - ((y - 1) * G.nxo + (x - 1)) : 0;
+        d.g[x][c] = *(const floatx4 *)(gp + (int64_t)o * C);
+      }
+  };
+  floatx4 lo[NC], mid[NC], hi[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) lo[c] = mid[c] = hi[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+  Row cur, nxt;
+  const std::integral_constant<int, 0> y0;
+  const std::integral_constant<int, 1> y1;
+  const std::integral_constant<int, 2> y2;
+  load(max(k0 - 1, 0), y0, cur);
+  for (int p = max(k0 - 1, 0); p <= k1; ++p) {
+    const bool first = p == 0, last = p == G.nz - 1;
+    auto use = [&](auto yc, const Row &d) __attribute__((always_inline)) {
+      constexpr int y = decltype(yc)::value;
+#pragma unroll
+      for (int x = 0; x < 3; ++x) {
+        constexpr int t0 = 3 * y;
+        const int t = t0 + x;
+        floatx4 g[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          g[c] = (ok[c] >> t) & 1u ? d.g[x][c] : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            lo[c] = mfma32f(w[t][m], g[c][m], lo[c]);
+            mid[c] = mfma32f(w[9 + t][m], g[c][m], mid[c]);
+            hi[c] = mfma32f(w[18 + t][m], g[c][m], hi[c]);
+          }
+        if (first) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) mid[c] = mfma32f(w[t][m], g[c][m], mid[c]);
+        }
+        if (last) {
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) mid[c] = mfma32f(w[18 + t][m], g[c][m], mid[c]);
+        }
+      }
+    };
+    if (p < G.nz) {
+      load(p, y1, nxt);
+      use(y0, cur);
+      load(p, y2, cur);
+      use(y1, nxt);
+      load(p + 1, y0, nxt);
+      use(y2, cur);
+      cur = nxt;
+    }
+    if (p > k0) {  // level p - 1 is complete
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (cell[c] < plane_in) {
+          const int64_t q = (((int64_t)b * G.nz + p - 1) * plane_in + cell[c]) * C + 4 * quad;
+          const uint2 s = *(const uint2 *)(ain + q);
+          floatx4 v;
+          v[0] = lo[c][0] * ((s.x & 0x8000u) ? alpha : 1.f);
+          v[1] = lo[c][1] * ((s.x & 0x80000000u) ? alpha : 1.f);
+          v[2] = lo[c][2] * ((s.y & 0x8000u) ? alpha : 1.f);
+          v[3] = lo[c][3] * ((s.y & 0x80000000u) ? alpha : 1.f);
+          *(floatx4 *)(gprev + q) = v;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      lo[c] = mid[c];
+      mid[c] = hi[c];
+      hi[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+}
+
+// Layer 3 (16 -> 1): a thread per input cell, its 16 channels.
+__global__ __launch_bounds__(kBlock) void dgrad_last_kernel(CnnGeom G, const float *__restrict__ gy,
+                                                            const uint16_t *__restrict__ wl,
+                                                            const uint16_t *__restrict__ ain,
+                                                            float alpha,
+                                                            float *__restrict__ gprev) {
+  constexpr int C = kCnnCh;
+  __shared__ float w[kCnnTaps * C];
+  for (int e = threadIdx.x; e < kCnnTaps * C; e += blockDim.x) w[e] = bf2f(wl[e]);
   __syncthreads();
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= G.n_in) return;
   const Cell c = decode(q, G.nz, G.nyi, G.nxi);
-  float acc[CI];
+  float acc[C];
 #pragma unroll
-  for (int i = 0; i < CI; ++i) acc[i] = 0.f;
+  for (int i = 0; i < C; ++i) acc[i] = 0.f;
   for (int dz = -1; dz <= 1; ++dz) {
     int ks[2], nk = 0;
     if (c.k - dz >= 0 && c.k - dz < G.nz) ks[nk++] = c.k - dz;
@@ -841,85 +1002,294 @@ __global__ __launch_bounds__(kBlock) void dgrad_kernel(CnnGeom G, const float *_
       for (int dx = -1; dx <= 1; ++dx) {
         const int i = c.i - 1 - dx;
         if (i < 0 || i >= G.nxo) continue;
-        const int t = 9 * (dz + 1) + 3 * (dy + 1) + (dx + 1);
+        const float *wr = w + (9 * (dz + 1) + 3 * (dy + 1) + (dx + 1)) * C;
         for (int m = 0; m < nk; ++m) {
-          const float *g = gy + ((((int64_t)c.b * G.nz + ks[m]) * G.nyo + j) * G.nxo + i) * CO;
-#pragma unroll 2
-          for (int o = 0; o < CO; ++o) {
-            const float gv = g[o];
-            const float *wr = w + (t * CO + o) * CI;
+          const float gv = gy[(((int64_t)c.b * G.nz + ks[m]) * G.nyo + j) * G.nxo + i];
 #pragma unroll
-            for (int i2 = 0; i2 < CI; ++i2) acc[i2] += gv * wr[i2];
-          }
+          for (int i2 = 0; i2 < C; ++i2) acc[i2] += gv * wr[i2];
         }
       }
     }
   }
 #pragma unroll
-  for (int i = 0; i < CI; ++i) {
-    const bool neg = (ain[q * CI + i] & 0x8000u) != 0;
-    gprev[q * CI + i] = acc[i] * (neg ? alpha : 1.f);
+  for (int i = 0; i < C; ++i) {
+    const bool neg = (ain[q * C + i] & 0x8000u) != 0;
+    gprev[q * C + i] = acc[i] * (neg ? alpha : 1.f);
   }
 }
 
-// Weight gradient partials of one block of `chunk` output cells: thread
-// pair (o, i) accumulates the 27 taps in FP64 (products of an FP32 gradient
-// and a bfloat16 activation are exact in FP64); PAIRS < 256 spreads the
-// cells over 256 / PAIRS groups, summed in a fixed order through LDS.
-// Partials layout per block: [tap][o][i] then the CO bias entries.
-template <int CI, int CO>
-__global__ __launch_bounds__(kBlock) void wgrad_kernel(CnnGeom G, const float *__restrict__ gy,
-                                                       const uint16_t *__restrict__ ain,
-                                                       int64_t chunk, double *__restrict__ partials) {
-  constexpr int PAIRS = CI * CO;
-  constexpr int GROUPS = kBlock / PAIRS;
-  constexpr int E = kCnnTaps * PAIRS + CO;
-  __shared__ double red[kBlock];
-  const int pair = threadIdx.x % PAIRS, grp = threadIdx.x / PAIRS;
-  const int o = pair / CI, ci = pair % CI;
-  double acc[kCnnTaps + 1];
+// ---- weight gradients on the matrix cores
+// dW(o, i) = sum over cells of g(cell, o) a(cell + tap, i): per tap a product
+// of a 16 x cells and a cells x 16 matrix.  The sums are FP64 (an FP32
+// gradient times a bfloat16 activation is exact there), so the product is
+// v_mfma_f64_16x16x4: four cells a step, lane l holding channel l % 16 of
+// cell l / 16 of both operands and entries (4 r + l / 16, l % 16), r = 0..3,
+// of the result.  The four cells of a step may be any four: lane group l / 16
+// walks along its own x row, so that a value read for one step serves the
+// next steps' other dx taps and is read and converted once.
+// Bound by the FP64 matrix rate (44 to 57 TFLOP/s measured).  16 crops of 42
+// x 42 x 128, layers 1 and 2 together: 22.4 ms with a thread per (o, i) and a
+// load and conversion of both factors per product; 1.35 ms here. The first and
+// last layers 0.87 and 0.64 ms before, 0.115 and 0.108 ms here.
+
+// Rows [r0, r1) of four-row groups that block blockIdx.x takes: XCD x takes
+// the x-th contiguous part, so that the rows above and below come from its
+// L2.
+__device__ __forceinline__ RowRange quad_range(int64_t rows) { return xcd_rows((rows + 3) / 4); }
+
+constexpr int kWgradNT = 768;  // 3 dz x 4 row groups of waves
+
+__global__ __launch_bounds__(kWgradNT) void wgrad_mid_kernel(CnnGeom G,
+                                                             const float *__restrict__ gy,
+                                                             const uint16_t *__restrict__ ain,
+                                                             double *__restrict__ partials) {
+  constexpr int C = kCnnCh, E = kCnnTaps * C * C + C;
+  __shared__ double red[E];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ch = lane & 15, kq = lane >> 4, zt = wv % 3, grp = wv / 3;
+  doublex4 acc[9];
 #pragma unroll
-  for (int t = 0; t <= kCnnTaps; ++t) acc[t] = 0.0;
-  const int64_t c0 = (int64_t)blockIdx.x * chunk;
-  const int64_t c1 = c0 + chunk < G.n_out ? c0 + chunk : G.n_out;
-  // threads beyond GROUPS * PAIRS (PAIRS not dividing the block) stay idle
-  for (int64_t q = c0 + grp; grp < GROUPS && q < c1; q += GROUPS) {
-    const Cell c = decode(q, G.nz, G.nyo, G.nxo);
-    const double g = gy[q * CO + o];
-    acc[kCnnTaps] += g;
+  for (int t = 0; t < 9; ++t) acc[t] = doublex4{0., 0., 0., 0.};
+  double bsum = 0.0;
+  const int64_t rows = (int64_t)G.batch * G.nz * G.nyo;
+  const RowRange rr = quad_range(rows);
+  for (int64_t q = rr.r0 + grp; q < rr.r1; q += kWgradNT / 192) {
+    const bool in = 4 * q + kq < rows;  // past the last row: zeros
+    const int64_t r = in ? 4 * q + kq : rows - 1;
+    const int64_t bk = r / G.nyo;
+    const int j = (int)(r - bk * G.nyo), k = (int)(bk % G.nz);
+    const int kk = min(max(k + zt - 1, 0), G.nz - 1);
+    const float *gp = gy + r * G.nxo * C + ch;
+    const uint16_t *ap = ain + ((bk - k + kk) * G.nyi + j) * G.nxi * C + ch;
+    const int ys = G.nxi * C;
+    // three steps' values ahead: the gradient of cells s .. s + 2 and the
+    // activations of columns s + 2 .. s + 4
+    float g[3];
+    uint16_t a[3][3];
+    auto load = [&](int s) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < kCnnTaps; ++t) {
-      const int64_t src = src_cell(G, c, t / 9 - 1, (t / 3) % 3 - 1, t % 3 - 1);
-      acc[t] += g * (double)bf2f(ain[src * CI + ci]);
+      for (int u = 0; u < 3; ++u) {
+        g[u] = gp[min(s + u, G.nxo - 1) * C];
+#pragma unroll
+        for (int y = 0; y < 3; ++y) a[y][u] = ap[y * ys + min(s + u + 2, G.nxi - 1) * C];
+      }
+    };
+    auto value = [&](uint16_t v) { return (double)bf2f(in ? v : (uint16_t)0); };
+    double win[3][3];  // activations of rows j .. j + 2, column x in slot x % 3
+#pragma unroll
+    for (int y = 0; y < 3; ++y) {
+      win[y][0] = value(ap[y * ys]);
+      win[y][1] = value(ap[y * ys + C]);
+    }
+    load(0);
+    for (int s = 0; s < G.nxo; s += 3) {
+      double gv[3], av[3][3];
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        gv[u] = in ? (double)g[u] : 0.0;
+#pragma unroll
+        for (int y = 0; y < 3; ++y) av[y][u] = value(a[y][u]);
+      }
+      if (s + 3 < G.nxo) load(s + 3);
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        if (s + u >= G.nxo) break;
+        bsum += gv[u];
+#pragma unroll
+        for (int y = 0; y < 3; ++y) {
+          win[y][(u + 2) % 3] = av[y][u];
+#pragma unroll
+          for (int x = 0; x < 3; ++x)
+            acc[3 * y + x] = mfma64(gv[u], win[y][(u + x) % 3], acc[3 * y + x]);
+        }
+      }
     }
   }
-  double *out = partials + (int64_t)blockIdx.x * E;
-  for (int t = 0; t <= kCnnTaps; ++t) {
-    double v = acc[t];
-    if (GROUPS > 1) {
-      __syncthreads();
-      red[threadIdx.x] = v;
-      __syncthreads();
-      if (grp == 0)
-        for (int m = 1; m < GROUPS; ++m) v += red[m * PAIRS + pair];
+  bsum += __shfl_xor(bsum, 16);
+  bsum += __shfl_xor(bsum, 32);
+  // the row groups' sums, in order
+  for (int w = 0; w < kWgradNT / 192; ++w) {
+    if (grp == w) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double *d = red + (9 * zt + t) * C * C + (4 * v + kq) * C + ch;
+          *d = (w ? *d : 0.0) + acc[t][v];
+        }
+      if (zt == 1 && kq == 0) {
+        double *d = red + kCnnTaps * C * C + ch;
+        *d = (w ? *d : 0.0) + bsum;
+      }
     }
-    if (grp == 0) {
-      if (t < kCnnTaps)
-        out[t * PAIRS + pair] = v;
-      else if (ci == 0)
-        out[kCnnTaps * PAIRS + o] = v;
-    }
+    __syncthreads();
   }
+  for (int e = threadIdx.x; e < E; e += kWgradNT) partials[(int64_t)blockIdx.x * E + e] = red[e];
 }
 
+// The first (CI -> 16) and last (16 -> 1) layer: one operand is the 16
+// channels of a cell, the columns of the other are the layer's 27 taps (times
+// CI), read as single values.
+// First: cells are outputs, the 16 channels their gradient, column (tap, c)
+// the input value the tap reads.  Last: cells are inputs, the 16 channels
+// their activation, column tap the gradient of the output that reads the
+// cell through that tap (two of them where z mirrors, none past the edges).
+// 1024 threads (CI = 1) or 512 (CI = 3, whose six column tiles take twice the
+// registers); the values of the next U steps are read while
+// these are multiplied.
+template <int CI>
+constexpr int kWgradEdgeNT = CI == 1 ? 1024 : 512;
+
+template <int CI, bool LAST>
+__global__ __launch_bounds__(kWgradEdgeNT<CI>) void wgrad_edge_kernel(
+    CnnGeom G, const float *__restrict__ gy, const uint16_t *__restrict__ ain,
+    double *__restrict__ partials) {
+  constexpr int C = kCnnCh, COLS = kCnnTaps * CI, NT = (COLS + 15) / 16;
+  constexpr int E = kCnnTaps * CI * C + (LAST ? 1 : C), NTH = kWgradEdgeNT<CI>,
+                NW = NTH / 64, U = NTH / 256;
+  static_assert(!LAST || CI == 1, "the last layer has one gradient per cell");
+  __shared__ double red[E];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ch = lane & 15, kq = lane >> 4;
+  doublex4 acc[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) acc[n] = doublex4{0., 0., 0., 0.};
+  double bsum = 0.0;
+  const int ny = LAST ? G.nyi : G.nyo, nx = LAST ? G.nxi : G.nxo;
+  const int64_t rows = (int64_t)G.batch * G.nz * ny;
+  const RowRange rr = quad_range(rows);
+  for (int64_t q = rr.r0 + wv; q < rr.r1; q += NW) {
+    const bool in = 4 * q + kq < rows;
+    const int64_t r = in ? 4 * q + kq : rows - 1;
+    const int64_t bk = r / ny;
+    const int j = (int)(r - bk * ny), k = (int)(bk % G.nz);
+    const int64_t b0 = bk - k;
+    // column n of this lane: its row(s) and the x shift of its tap; `two`:
+    // the second row that a mirrored level adds
+    int64_t at[NT], at2[NT];
+    int shift[NT];
+    bool has[NT], two[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int col = min(16 * n + ch, COLS - 1), t = col / CI, c = col - t * CI;
+      const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
+      has[n] = in && 16 * n + ch < COLS;
+      two[n] = false;
+      at2[n] = 0;
+      if constexpr (LAST) {
+        const int jo = j - 1 - dy, ko = k - dz;
+        const bool y = has[n] && jo >= 0 && jo < G.nyo;
+        has[n] = y && ko >= 0 && ko < G.nz;
+        two[n] = y && ((dz < 0 && k == 0) || (dz > 0 && k == G.nz - 1));
+        at[n] = has[n] ? ((b0 + ko) * G.nyo + jo) * G.nxo : 0;
+        at2[n] = two[n] ? (bk * G.nyo + jo) * G.nxo : 0;
+        shift[n] = -1 - dx;
+      } else {
+        const int kk = min(max(k + dz, 0), G.nz - 1);
+        at[n] = (((b0 + kk) * G.nyi + j + 1 + dy) * G.nxi + 1 + dx) * CI + c;
+        shift[n] = 0;
+      }
+    }
+    // raw values of steps s .. s + U - 1, zero past the row
+    using Wide = std::conditional_t<LAST, uint16_t, float>;
+    using Col = std::conditional_t<LAST, float, uint16_t>;
+    Wide rw[U];
+    Col rc[NT][U], rc2[LAST ? NT : 1][LAST ? U : 1];
+    auto load = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int x = min(s + u, nx - 1);
+        const bool inx = in && s + u < nx;
+        const int64_t w = (r * nx + x) * C + ch;
+        if constexpr (LAST)
+          rw[u] = inx ? ain[w] : Wide(0);
+        else
+          rw[u] = inx ? gy[w] : Wide(0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          if constexpr (LAST) {
+            const int xo = x + shift[n];
+            const bool v = inx && xo >= 0 && xo < G.nxo;
+            rc[n][u] = v && has[n] ? gy[at[n] + xo] : Col(0);
+            rc2[n][u] = v && two[n] ? gy[at2[n] + xo] : Col(0);
+          } else {
+            rc[n][u] = inx && has[n] ? ain[at[n] + (int64_t)x * CI] : Col(0);
+          }
+        }
+      }
+    };
+    load(0);
+    for (int s = 0; s < nx; s += U) {
+      double wide[U], col[NT][U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if constexpr (LAST)
+          wide[u] = (double)bf2f(rw[u]);
+        else
+          wide[u] = (double)rw[u];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          if constexpr (LAST)
+            col[n][u] = (double)rc[n][u] + (double)rc2[n][u];
+          else
+            col[n][u] = (double)bf2f(rc[n][u]);
+        }
+      }
+      if (s + U < nx) load(s + U);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // the bias: the gradient's own sum (last: what the centre tap reads)
+        bsum += LAST ? col[0][u] : wide[u];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[n] = mfma64(wide[u], col[n][u], acc[n]);
+      }
+    }
+  }
+  bsum += __shfl_xor(bsum, 16);
+  bsum += __shfl_xor(bsum, 32);
+  for (int w = 0; w < NW; ++w) {
+    if (wv == w) {
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int col = 16 * n + ch, t = col / CI, c = col - t * CI, row = 4 * v + kq;
+          if (col < COLS) {
+            double *d = red + (t * C + row) * CI + c;
+            *d = (w ? *d : 0.0) + acc[n][v];
+          }
+        }
+      if (kq == 0 && (!LAST || ch == kCnnTaps / 2)) {
+        double *d = red + kCnnTaps * CI * C + (LAST ? 0 : ch);
+        *d = (w ? *d : 0.0) + bsum;
+      }
+    }
+    __syncthreads();
+  }
+  for (int e = threadIdx.x; e < E; e += NTH)
+    partials[(int64_t)blockIdx.x * E + e] = red[e];
+}
+
+// Sums of the blocks' partials: eight threads per entry, each a run of the
+// blocks, then their sums in order.
 __global__ __launch_bounds__(kBlock) void wgrad_final_kernel(const double *__restrict__ partials,
-                                                             int nblocks, int E, int nw,
+                                                             int E, int nw,
                                                              float *__restrict__ gw,
                                                              float *__restrict__ gb) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= E) return;
+  constexpr int P = 8, N = kBlock / P;
+  static_assert(kCnnWgradBlocks % P == 0, "blocks split evenly");
+  __shared__ double red[P][N];
+  const int le = threadIdx.x % N, part = threadIdx.x / N, e = blockIdx.x * N + le;
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partials[(int64_t)b * E + e];
+  if (e < E) {
+#pragma unroll 8
+    for (int b = 0; b < kCnnWgradBlocks / P; ++b)
+      s += partials[(int64_t)(part * (kCnnWgradBlocks / P) + b) * E + e];
+  }
+  red[part][le] = s;
+  __syncthreads();
+  if (part != 0 || e >= E) return;
+  for (int m = 1; m < P; ++m) s += red[m][le];
   if (e < nw)
     gw[e] = (float)s;
   else
@@ -1196,30 +1566,34 @@ void launch_cnn_loss(int batch, int nz, int ny, int nx, double wx, double wy, do
 void launch_cnn_dgrad(int layer, const CnnGeom &G, const float *gy, const uint16_t *wbf,
                       const uint16_t *ain, float alpha, float *gprev, hipStream_t s) {
   const uint16_t *wl = wbf + cnn_weight_offset(G.inputs, layer);
-  if (layer == kCnnLayers - 1)
-    dgrad_kernel<kCnnCh, 1><<<blocks_for(G.n_in), kBlock, 0, s>>>(G, gy, wl, ain, alpha, gprev);
-  else
-    dgrad_kernel<kCnnCh, kCnnCh><<<blocks_for(G.n_in), kBlock, 0, s>>>(G, gy, wl, ain, alpha,
-                                                                        gprev);
+  if (layer == kCnnLayers - 1) {
+    dgrad_last_kernel<<<blocks_for(G.n_in), kBlock, 0, s>>>(G, gy, wl, ain, alpha, gprev);
+    return;
+  }
+  const int cells = 16 * kDgradChains, tasks = (G.nyi * G.nxi + cells - 1) / cells;
+  // two waves on a SIMD
+  const int levels = chunk_levels((int64_t)tasks * G.batch, G.nz, kDgradLevels, 2048);
+  const int chunks = (G.nz + levels - 1) / levels;
+  const int64_t waves = (int64_t)tasks * chunks * G.batch;
+  dgrad_mid_kernel<<<(unsigned)((waves + 31) / 32 * 8), 256, 0, s>>>(
+      G, gy, wl, ain, alpha, gprev, tasks, levels, chunks);
 }
 
 void launch_cnn_wgrad(int layer, const CnnGeom &G, const float *gy, const uint16_t *ain,
                       double *partials, float *grad, hipStream_t s) {
   const int ci = cnn_cin(G.inputs, layer), co = cnn_cout(layer);
-  const int E = kCnnTaps * ci * co + co;
-  const int64_t chunk = (G.n_out + kCnnWgradBlocks - 1) / kCnnWgradBlocks;
+  const int nw = kCnnTaps * ci * co, E = nw + co;
   if (ci == 1)
-    wgrad_kernel<1, kCnnCh><<<kCnnWgradBlocks, kBlock, 0, s>>>(G, gy, ain, chunk, partials);
+    wgrad_edge_kernel<1, false><<<kCnnWgradBlocks, kWgradEdgeNT<1>, 0, s>>>(G, gy, ain, partials);
   else if (ci == 3)
-    wgrad_kernel<3, kCnnCh><<<kCnnWgradBlocks, kBlock, 0, s>>>(G, gy, ain, chunk, partials);
+    wgrad_edge_kernel<3, false><<<kCnnWgradBlocks, kWgradEdgeNT<3>, 0, s>>>(G, gy, ain, partials);
   else if (co == 1)
-    wgrad_kernel<kCnnCh, 1><<<kCnnWgradBlocks, kBlock, 0, s>>>(G, gy, ain, chunk, partials);
+    wgrad_edge_kernel<1, true><<<kCnnWgradBlocks, kWgradEdgeNT<1>, 0, s>>>(G, gy, ain, partials);
   else
-    wgrad_kernel<kCnnCh, kCnnCh><<<kCnnWgradBlocks, kBlock, 0, s>>>(G, gy, ain, chunk, partials);
-  wgrad_final_kernel<<<blocks_for(E), kBlock, 0, s>>>(partials, kCnnWgradBlocks, E,
-                                                      kCnnTaps * ci * co,
-                                                      grad + cnn_weight_offset(G.inputs, layer),
-                                                      grad + cnn_bias_offset(G.inputs, layer));
+    wgrad_mid_kernel<<<kCnnWgradBlocks, kWgradNT, 0, s>>>(G, gy, ain, partials);
+  wgrad_final_kernel<<<(E + 31) / 32, kBlock, 0, s>>>(partials, E, nw,
+                                                     grad + cnn_weight_offset(G.inputs, layer),
+                                                     grad + cnn_bias_offset(G.inputs, layer));
 }
 
 void launch_cnn_adam(int n, float *params, const float *grad, float *m, float *v, int step,

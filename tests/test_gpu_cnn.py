@@ -546,3 +546,32 @@ def test_forward_does_not_depend_on_the_chunk_length(gpu, periodic, nz, ny, nx):
     many, _ = gpu.forward(prm, packed, x.repeat(400, 1, 1, 1).contiguous(), periodic=periodic,
                           alpha=0.1)
     assert torch.equal(many, one.expand_as(many))
+
+
+# rows that do not fill the groups of four, planes that do not fill the chains
+# of 16 cells, one to many z chunks, a single level (both mirrors at once)
+@pytest.mark.parametrize("shape", [(1, 1, 1, 11, 11), (1, 1, 2, 12, 14), (3, 1, 37, 11, 13),
+                                   (2, 1, 70, 19, 26), (1, 3, 1, 11, 12), (2, 3, 9, 13, 11)])
+def test_backward_at_the_edges_of_its_tiles(gpu, shape):
+    """As test_backward_matches_oracle_on_identical_operands, <= 1e-5 per
+    layer."""
+    from oracle import cnn as ocnn
+    batch, C, nz, ny, nx = shape
+    p = params(30) if C == 1 else params3(30)
+    rng = np.random.default_rng(31)
+    x = rng.standard_normal(shape).astype(np.float32).astype(float)
+    if C == 1:
+        x = x[:, 0]
+    P = _t(p)
+    packed = gpu.pack(P)
+    out, work = gpu.forward(P, packed, _t(x), periodic=False, alpha=0.1)
+    acts = [np.ascontiguousarray(_np(gpu.stored_input(x.shape, work, l, alpha=0.1)))
+            for l in range(4)]
+    gout = rng.standard_normal(_np(out).shape).astype(np.float32).astype(float)
+    ref = ocnn.backward(p, x, acts, [acts[1], acts[2], acts[3]], gout, periodic=False, alpha=0.1)
+    got = _np(gpu.backward(x.shape, packed, work, _t(gout), alpha=0.1))
+    for l in range(4):
+        a, b = ocnn.weight_offset(l, C), ocnn.bias_offset(l, C)
+        e = b + (16 if l < 3 else 1)
+        assert rel(got[a:b], ref[a:b]) <= 1e-5, (l, rel(got[a:b], ref[a:b]))
+        assert rel(got[b:e], ref[b:e]) <= 1e-5, (l, "bias")
