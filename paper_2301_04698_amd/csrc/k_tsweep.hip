@@ -1,6 +1,6 @@
 // Weighted-Jacobi / Chebyshev sweeps of the compact 7-point
-// pressure-correction operator (paper Sec. 2.4 and App. A), one or two
-// sweeps per launch.
+// pressure-correction operator (paper Sec. 2.4 and App. A), one sweep per
+// launch.
 //
 // The point update is les_sweep.h's, so the iterates of every kernel are
 // bitwise equal.
@@ -16,11 +16,6 @@
 // iterate's neighbour rows.  Narrower grids take 64 x 4 (or 64 x 16
 // streamed, 64 x 1 for ny < 4) tiles.
 //
-// Two sweeps: one wave per four rows and 62-cell segment also forms the
-// first sweep of the two rows beside them in registers, so the second sweep
-// needs no LDS and no barrier; 20 bytes per cell from memory for both
-// sweeps (phi, prev, rhs in; the two new iterates out).
-//
 // Walls: the z neighbour of the bottom/top level is that level itself (even
 // mirror); x and y are periodic.
 #include "les_column.h"
@@ -29,11 +24,6 @@
 namespace lesmi {
 
 namespace {
-
-__device__ __forceinline__ int pmod(int i, int n) {
-  int r = i % n;
-  return r < 0 ? r + n : r;
-}
 
 // Logical tile of physical block b.  Workgroups go to the 8 XCDs
 // round-robin (b mod 8); each XCD gets one contiguous range of tiles
@@ -49,13 +39,12 @@ struct SweepArgs {
   Grid g;
   SweepCoef k;
   int kc, tiles_x, tiles_y, tiles_z, ntiles;
-  double wc0, wc1;   // Chebyshev weights of the launch's first and second sweep
-  int first;         // the first sweep is the first of the solve (weight 1, no prev)
+  double wc0;        // Chebyshev weight
   const T *cur, *prev, *rhs;
-  T *out_last, *out_prev;
+  T *out;
   SolveCtl *ctl;
   double *partials;
-  // one-sweep launches: a pending residual check (sweep dec_m >= 0) of an
+  // a pending residual check (sweep dec_m >= 0) of an
   // earlier launch whose dec_np block partials block 0 reduces and decides
   const double *dec_partials;
   int dec_np, dec_m;
@@ -142,9 +131,9 @@ __device__ __forceinline__ double march_row(const SweepArgs<T> &a, const TileIdx
     const T out = (T)point_update(a.k, (double)c, res, CHEB, pv, a.wc0);
     if (valid) {
       if (NT)
-        __builtin_nontemporal_store(out, &a.out_last[q]);
+        __builtin_nontemporal_store(out, &a.out[q]);
       else
-        a.out_last[q] = out;
+        a.out[q] = out;
     }
     below = c;
     c = above;
@@ -206,176 +195,10 @@ __global__ __launch_bounds__(64 * WX * TY) void sweep1_kernel(SweepArgs<T> a) {
   }
 }
 
-// --------------------------------------------------------------- 2 sweeps
-
-// Two fused sweeps without LDS or barriers.  A wave owns R rows j0 ..
-// j0+R-1 and a 62-cell x segment (lanes 1..62; lanes 0 and 63 are its halo
-// columns, wrapped periodically like every other lane) of the z chunk
-// [k0, k1).  Marching up z it forms the first sweep on rows j0-1 .. j0+R at
-// level k (their y neighbours are rows j0-2 .. j0+R+1 of the iterate, x
-// neighbours the adjacent lanes, z neighbours registers), then the second
-// sweep on its R rows at level k-1 from first-sweep values that are all in
-// its own registers or adjacent lanes.  The first sweep of the two boundary
-// rows is also formed by the neighbouring waves; in exchange every array is
-// read from memory once per two sweeps (neighbour rows through the caches).
-// All accesses are buffer loads and stores on one z plane: lanes outside
-// the segment's core, and rows beyond the grid, store at an offset past the
-// plane's range, which the hardware drops.
-constexpr int kR2 = 4;  // rows per wave of the two-sweep kernel
-
-template <typename T, int R, bool CHEB, bool CHECK>
-__global__ __launch_bounds__(256) void sweep2_kernel(SweepArgs<T> a) {
-  if (a.ctl->done) return;
-  constexpr int NR = R + 2;  // first-sweep rows j0-1 .. j0+R
-  const Grid &g = a.g;
-  const int lb = xcd_tile(blockIdx.x, gridDim.x);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int lane = (int)(threadIdx.x & 63);
-  const int u = lb * 4 + wave;
-  double acc = 0.0;
-  if (u < a.ntiles) {  // uniform per wave
-    const int ty = u % a.tiles_y, rest = u / a.tiles_y;
-    const int tx = rest % a.tiles_x, tz = rest / a.tiles_x;
-    const int j0 = ty * R;
-    const int k0 = tz * a.kc, k1 = min(g.nz, k0 + a.kc);
-    const int xu = tx * 62 - 1 + lane;
-    const bool core = lane >= 1 && lane <= 62 && xu < g.nx;
-    const int i = pmod(xu, g.nx), il = pmod(xu - 1, g.nx), ir = pmod(xu + 1, g.nx);
-    constexpr uint32_t kOut = 0x80000000u;  // beyond any plane (at most 2 GiB)
-    const uint32_t es = (uint32_t)sizeof(T);
-    uint32_t o[R + 4];  // rows j0-2 .. j0+R+1 of this lane's column
-#pragma unroll
-    for (int d = 0; d < R + 4; ++d)
-      o[d] = ((uint32_t)i + (uint32_t)g.nx * (uint32_t)pmod(j0 + d - 2, g.ny)) * es;
-    uint32_t oxl[NR], oxr[NR];  // x neighbours of the end lanes
-#pragma unroll
-    for (int d = 0; d < NR; ++d) {
-      const uint32_t row = (uint32_t)g.nx * (uint32_t)pmod(j0 + d - 1, g.ny);
-      oxl[d] = lane == 0 ? ((uint32_t)il + row) * es : kOut;
-      oxr[d] = lane == 63 ? ((uint32_t)ir + row) * es : kOut;
-    }
-    uint32_t ost[R];  // store offsets of the output rows
-    bool rcore[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      rcore[r] = core && j0 + r < g.ny;
-      ost[r] = rcore[r] ? o[r + 2] : kOut;
-    }
-    const int64_t pb = g.nxy * (int64_t)sizeof(T);
-    const bool cheb1 = CHEB && !a.first;
-    const int kb = max(0, k0 - 1), ke = min(g.nz - 1, k1);
-    // iterate of the first-sweep rows at levels k-1 (bl) and k (cc)
-    T bl[NR], cc[NR];
-    {
-      const __amdgpu_buffer_rsrc_t rb = plane_rsrc(a.cur, pb, kb > 0 ? kb - 1 : 0);
-      const __amdgpu_buffer_rsrc_t rc = plane_rsrc(a.cur, pb, kb);
-#pragma unroll
-      for (int d = 0; d < NR; ++d) {
-        bl[d] = rsrc_load<T>(rb, o[d + 1]);
-        cc[d] = rsrc_load<T>(rc, o[d + 1]);
-      }
-    }
-    // first-sweep values at level k-1 (all rows) and k-2 (output rows);
-    // rhs and iterate of the output rows at level k-1
-    T s1p[NR], s1pp[R], rm1[R], cm1[R];
-#pragma unroll
-    for (int d = 0; d < NR; ++d) s1p[d] = T(0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) s1pp[r] = rm1[r] = cm1[r] = T(0);
-    for (int k = kb; k <= ke; ++k) {
-      const __amdgpu_buffer_rsrc_t rk = plane_rsrc(a.cur, pb, k);
-      const __amdgpu_buffer_rsrc_t ra = plane_rsrc(a.cur, pb, k + 1 < g.nz ? k + 1 : k);
-      const __amdgpu_buffer_rsrc_t rr = plane_rsrc(a.rhs, pb, k);
-      T ab[NR], rh[NR], pv[NR], xl[NR], xr[NR];
-#pragma unroll
-      for (int d = 0; d < NR; ++d) {
-        ab[d] = rsrc_load<T>(ra, o[d + 1]);
-        rh[d] = rsrc_load<T>(rr, o[d + 1]);
-        xl[d] = rsrc_load<T>(rk, oxl[d]);
-        xr[d] = rsrc_load<T>(rk, oxr[d]);
-        pv[d] = T(0);
-      }
-      const T ylo = rsrc_load<T>(rk, o[0]), yhi = rsrc_load<T>(rk, o[R + 3]);
-      if (cheb1) {
-        const __amdgpu_buffer_rsrc_t rp = plane_rsrc(a.prev, pb, k);
-#pragma unroll
-        for (int d = 0; d < NR; ++d) pv[d] = rsrc_load<T>(rp, o[d + 1]);
-      }
-      const bool core_k = k >= k0 && k < k1;
-      // ---- first sweep, rows j0-1 .. j0+R at level k
-      T s1[NR];
-#pragma unroll
-      for (int d = 0; d < NR; ++d) {
-        const T sp = lane_shift<1>(cc[d]), sm = lane_shift<-1>(cc[d]);
-        const T xp = lane == 63 ? xr[d] : sp;
-        const T xm = lane == 0 ? xl[d] : sm;
-        const T yp = d == NR - 1 ? yhi : cc[d < NR - 1 ? d + 1 : NR - 1];
-        const T ym = d == 0 ? ylo : cc[d > 0 ? d - 1 : 0];
-        const double hx = (double)xp + (double)xm;
-        const double hy = (double)yp + (double)ym;
-        const double hz = (double)ab[d] + (double)bl[d];
-        const double res = point_residual(a.k, (double)cc[d], hx, hy, hz, (double)rh[d]);
-        if (CHECK && d >= 1 && d <= R && core_k && rcore[d >= 1 && d <= R ? d - 1 : 0])
-          acc += res * res;
-        s1[d] = (T)point_update(a.k, (double)cc[d], res, cheb1, (double)pv[d], a.wc0);
-      }
-      if (CHEB && core_k) {
-        const __amdgpu_buffer_rsrc_t ro = plane_rsrc(a.out_prev, pb, k);
-#pragma unroll
-        for (int r = 0; r < R; ++r) rsrc_store<T>(ro, ost[r], s1[r + 1]);
-      }
-      // ---- second sweep, output rows at level k-1
-      if (k - 1 >= k0 && k - 1 < k1) {
-        const __amdgpu_buffer_rsrc_t ro = plane_rsrc(a.out_last, pb, k - 1);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const T ctr = s1p[r + 1];
-          const T lo = k - 1 == 0 ? ctr : s1pp[r];
-          const double h2x = (double)lane_shift<1>(ctr) + (double)lane_shift<-1>(ctr);
-          const double h2y = (double)s1p[r + 2] + (double)s1p[r];
-          const double h2z = (double)s1[r + 1] + (double)lo;
-          const double r2 = point_residual(a.k, (double)ctr, h2x, h2y, h2z, (double)rm1[r]);
-          rsrc_store<T>(ro, ost[r], (T)point_update(a.k, (double)ctr, r2, CHEB, (double)cm1[r], a.wc1));
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        s1pp[r] = s1p[r + 1];
-        rm1[r] = rh[r + 1];
-        cm1[r] = cc[r + 1];
-      }
-#pragma unroll
-      for (int d = 0; d < NR; ++d) {
-        s1p[d] = s1[d];
-        bl[d] = cc[d];
-        cc[d] = ab[d];
-      }
-    }
-    if (k1 == g.nz) {  // the top level: its upper neighbour is itself
-      const int kk = g.nz - 1;
-      const __amdgpu_buffer_rsrc_t ro = plane_rsrc(a.out_last, pb, kk);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const T ctr = s1p[r + 1];
-        const T lo = kk == 0 ? ctr : s1pp[r];
-        const double h2x = (double)lane_shift<1>(ctr) + (double)lane_shift<-1>(ctr);
-        const double h2y = (double)s1p[r + 2] + (double)s1p[r];
-        const double h2z = (double)ctr + (double)lo;
-        const double r2 = point_residual(a.k, (double)ctr, h2x, h2y, h2z, (double)rm1[r]);
-        rsrc_store<T>(ro, ost[r], (T)point_update(a.k, (double)ctr, r2, CHEB, (double)cm1[r], a.wc1));
-      }
-    }
-  }
-  if (CHECK) {
-    const double s = block_sum(acc);
-    if (threadIdx.x == 0) a.partials[blockIdx.x] = s;
-  }
-}
-
 struct Shape {
   int kc, tiles_x, tiles_y, tiles_z, ntiles, blocks;
-  int wx, ty;   // one-sweep kernel: waves along x, tile rows
-  bool stream;  // one-sweep kernel: streamed arrays
+  int wx, ty;   // waves along x, tile rows
+  bool stream;  // streamed arrays
 };
 
 // The four arrays of a sweep exceed what the Infinity Cache keeps.
@@ -383,42 +206,21 @@ bool streamed(const Grid &g, bool is_double) {
   return 4.0 * (double)g.n * (is_double ? 8.0 : 4.0) > 192.0e6;
 }
 
-Shape shape_of(const Grid &g, int S, bool is_double) {
+Shape shape_of(const Grid &g, bool is_double) {
   Shape sh;
-  sh.stream = S == 1 && streamed(g, is_double);
+  sh.stream = streamed(g, is_double);
   sh.wx = 1;
-  sh.ty = 0;
-  if (S == 1) {
-    int ty;
-    if (g.nx >= kWideNx && g.ny >= kWideTYBig) {
-      sh.wx = kWX;
-      ty = sh.stream ? kWideTYBig : kWideTY;
-    } else {
-      // rows beyond ny would idle: a short y axis (a two-dimensional run
-      // has ny = 1) takes the next smaller tile
-      ty = sh.stream ? kTY1Big : kTY1;
-      if (g.ny < ty) ty = g.ny < kTY1 ? 1 : kTY1;
-    }
-    sh.ty = ty;
-    sh.tiles_x = (g.nx + 64 * sh.wx - 1) / (64 * sh.wx);
-    sh.tiles_y = (g.ny + ty - 1) / ty;
+  if (g.nx >= kWideNx && g.ny >= kWideTYBig) {
+    sh.wx = kWX;
+    sh.ty = sh.stream ? kWideTYBig : kWideTY;
   } else {
-    // one wave per kR2 rows and 62-cell x segment, four waves per block; z
-    // chunks halved (to 8 levels at least) until about 8192 waves
-    sh.tiles_x = (g.nx + 61) / 62;
-    sh.tiles_y = (g.ny + kR2 - 1) / kR2;
-    const int64_t rows = (int64_t)sh.tiles_x * sh.tiles_y;
-    sh.kc = g.nz;
-    while (sh.kc > 8 && rows * ((g.nz + sh.kc - 1) / sh.kc) < 8192) sh.kc = (sh.kc + 1) / 2;
-    for (;;) {
-      sh.tiles_z = (g.nz + sh.kc - 1) / sh.kc;
-      if ((rows * sh.tiles_z + 3) / 4 <= kPartials) break;
-      sh.kc *= 2;
-    }
-    sh.ntiles = (int)(rows * sh.tiles_z);
-    sh.blocks = ((sh.ntiles + 3) / 4 + 7) / 8 * 8;
-    return sh;
+    // rows beyond ny would idle: a short y axis (a two-dimensional run has
+    // ny = 1) takes the next smaller tile
+    sh.ty = sh.stream ? kTY1Big : kTY1;
+    if (g.ny < sh.ty) sh.ty = g.ny < kTY1 ? 1 : kTY1;
   }
+  sh.tiles_x = (g.nx + 64 * sh.wx - 1) / (64 * sh.wx);
+  sh.tiles_y = (g.ny + sh.ty - 1) / sh.ty;
   const int64_t cols = (int64_t)sh.tiles_x * sh.tiles_y;
   // z chunks: long enough to amortise the halo planes, short enough for
   // several blocks per CU.  Wide tiles aim at a wave count: the 8192 waves
@@ -441,17 +243,14 @@ Shape shape_of(const Grid &g, int S, bool is_double) {
 
 }  // namespace
 
-int tsweep_blocks(const Grid &g, int S, bool is_double) {
-  return shape_of(g, S, is_double).blocks;
-}
+int tsweep_blocks(const Grid &g, bool is_double) { return shape_of(g, is_double).blocks; }
 
 template <typename T>
-void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
-                   double omega_jacobi, const double *omega_cheb, const T *cur, const T *prev,
-                   T *out_last, T *out_prev, const T *rhs, SolveCtl *ctl, double *partials,
-                   const double *dec_partials, int dec_np, int dec_m, int64_t *snap,
-                   int snap_seq, hipStream_t s) {
-  const Shape sh = shape_of(g, S, sizeof(T) == 8);
+void launch_tsweep(const Grid &g, bool chebyshev, bool check, bool first, double omega_jacobi,
+                   double omega_cheb, const T *cur, const T *prev, T *out, const T *rhs,
+                   SolveCtl *ctl, double *partials, const double *dec_partials, int dec_np,
+                   int dec_m, int64_t *snap, int snap_seq, hipStream_t s) {
+  const Shape sh = shape_of(g, sizeof(T) == 8);
   SweepArgs<T> a;
   a.g = g;
   a.k = sweep_coef(g, omega_jacobi);
@@ -460,20 +259,17 @@ void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
   a.tiles_y = sh.tiles_y;
   a.tiles_z = sh.tiles_z;
   a.ntiles = sh.ntiles;
-  a.wc0 = omega_cheb[0];
-  a.wc1 = S > 1 ? omega_cheb[1] : 1.0;
-  a.first = first ? 1 : 0;
+  a.wc0 = omega_cheb;
   a.cur = cur;
   a.prev = prev;
   a.rhs = rhs;
-  a.out_last = out_last;
-  a.out_prev = out_prev;
+  a.out = out;
   a.ctl = ctl;
   a.partials = partials;
   a.dec_partials = dec_partials;
   a.dec_np = dec_np;
-  a.dec_m = S == 1 ? dec_m : -1;
-  a.snap = a.dec_m >= 0 ? snap : nullptr;
+  a.dec_m = dec_m;
+  a.snap = dec_m >= 0 ? snap : nullptr;
   a.snap_seq = snap_seq;
   const dim3 grid(sh.blocks);
 #define LES_PICK(WX, TY, NT)                                                          \
@@ -487,41 +283,29 @@ void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
       else sweep1_kernel<T, WX, TY, false, false, NT><<<grid, block, 0, s>>>(a);      \
     }                                                                                 \
   } while (0)
-  if (S == 1) {
-    if (sh.wx == kWX && sh.stream)
-      LES_PICK(kWX, kWideTYBig, true);
-    else if (sh.wx == kWX)
-      LES_PICK(kWX, kWideTY, false);
-    else if (sh.ty == kTY1Big)
-      LES_PICK(1, kTY1Big, true);
-    else if (sh.ty == kTY1 && !sh.stream)
-      LES_PICK(1, kTY1, false);
-    else if (sh.ty == kTY1)
-      LES_PICK(1, kTY1, true);
-    else if (!sh.stream)
-      LES_PICK(1, 1, false);
-    else
-      LES_PICK(1, 1, true);
-  } else {
-    const dim3 block(256);
-    if (chebyshev) {
-      if (check) sweep2_kernel<T, kR2, true, true><<<grid, block, 0, s>>>(a);
-      else sweep2_kernel<T, kR2, true, false><<<grid, block, 0, s>>>(a);
-    } else {
-      if (check) sweep2_kernel<T, kR2, false, true><<<grid, block, 0, s>>>(a);
-      else sweep2_kernel<T, kR2, false, false><<<grid, block, 0, s>>>(a);
-    }
-  }
+  if (sh.wx == kWX && sh.stream)
+    LES_PICK(kWX, kWideTYBig, true);
+  else if (sh.wx == kWX)
+    LES_PICK(kWX, kWideTY, false);
+  else if (sh.ty == kTY1Big)
+    LES_PICK(1, kTY1Big, true);
+  else if (sh.ty == kTY1 && !sh.stream)
+    LES_PICK(1, kTY1, false);
+  else if (sh.ty == kTY1)
+    LES_PICK(1, kTY1, true);
+  else if (!sh.stream)
+    LES_PICK(1, 1, false);
+  else
+    LES_PICK(1, 1, true);
 #undef LES_PICK
 }
 
-template void launch_tsweep<float>(const Grid &, int, bool, bool, bool, double, const double *,
-                                   const float *, const float *, float *, float *, const float *,
-                                   SolveCtl *, double *, const double *, int, int, int64_t *, int,
-                                   hipStream_t);
-template void launch_tsweep<double>(const Grid &, int, bool, bool, bool, double, const double *,
-                                    const double *, const double *, double *, double *,
-                                    const double *, SolveCtl *, double *, const double *, int, int,
-                                    int64_t *, int, hipStream_t);
+#define LES_INST(T)                                                                            \
+  template void launch_tsweep<T>(const Grid &, bool, bool, bool, double, double, const T *,    \
+                                 const T *, T *, const T *, SolveCtl *, double *,              \
+                                 const double *, int, int, int64_t *, int, hipStream_t);
+LES_INST(float)
+LES_INST(double)
+#undef LES_INST
 
 }  // namespace lesmi

@@ -575,8 +575,13 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
   };
   auto launch_at = [&](int mm) {
     Launch L{mm, 1, is_check(mm)};
-    if (mm < max_sweeps)
-      while (L.S < smax && mm + L.S < max_sweeps && !is_check(mm + L.S)) ++L.S;
+    // the sweeps up to the next check, in launches as equal as they come
+    int64_t left = max_sweeps - mm;
+    if (fixed <= 0) left = std::min<int64_t>(left, every - mm % every);
+    if (left > 1) {
+      const int64_t n = (left + smax - 1) / smax;
+      L.S = (int)((left + n - 1) / n);
+    }
     return L;
   };
 
@@ -642,7 +647,7 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
     const Launch nextL = L.m + L.S <= max_sweeps ? launch_at(L.m + L.S) : Launch{-1, 0, false};
     const bool has_next = nextL.m >= 0;
     last_m = L.m;
-    const bool plain_full = !L.check && L.S == smax;
+    const bool plain_full = !L.check && L.m < max_sweeps;
     // a run starts at a plain launch after a check; every kTimeEvery-th run
     // is bracketed by events (each event costs the stream a few us)
     const bool run_start = plain_full && !prev_plain;
@@ -687,18 +692,22 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
     double *parts = (nchecks & 1) ? V.partials2 : V.partials;
     // The first Chebyshev sweep has weight 1: the plain weighted-Jacobi
     // sweep, which must not read the (uninitialised) previous iterate.
-    launch_tsweep<T>(g, L.S, cheb, L.check, L.m == 0, omega_j, wc, buf[cur],
-                     prev >= 0 ? buf[prev] : nullptr, buf[out_last],
-                     out_prev >= 0 ? buf[out_prev] : nullptr, rhs, V.ctl, parts,
-                     decides ? pend_parts : nullptr, decides ? pend_np : 0, decides ? pend_m : -1,
-                     decides ? h->poll_word_dev : nullptr, next_seq(), s);
+    if (L.S == 1)
+      launch_tsweep<T>(g, cheb, L.check, L.m == 0, omega_j, wc[0], buf[cur],
+                       prev >= 0 ? buf[prev] : nullptr, buf[out_last], rhs, V.ctl, parts,
+                       decides ? pend_parts : nullptr, decides ? pend_np : 0,
+                       decides ? pend_m : -1, decides ? h->poll_word_dev : nullptr, next_seq(), s);
+    else
+      launch_msweep<T>(g, L.S, cheb, L.check, L.m == 0, omega_j, wc, buf[cur],
+                       prev >= 0 ? buf[prev] : nullptr, buf[out_last], buf[out_prev], rhs, V.ctl,
+                       parts, s);
     if (L.S == 1) {
       prev = cur;
     } else {
       prev = out_prev;
     }
     cur = out_last;
-    const bool next_plain_full = has_next && !nextL.check && nextL.S == smax;
+    const bool next_plain_full = has_next && !nextL.check;
     if (timed && run_first >= 0 && !next_plain_full) {
       HIP_TRY(hipEventRecord(h->ev_sweep[2 * runs.size() + 1], s));
       runs.push_back(Run{run_first, L.m + L.S - 1});
@@ -713,8 +722,8 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
     if (L.check) {
       ++nchecks;
       // partial sums come from this launch's own block decomposition; the
-      // next launch decides unless it is a two-sweep launch or there is none
-      const int np = tsweep_blocks(g, L.S, sizeof(T) == 8);
+      // next launch decides if both are one-sweep launches
+      const int np = L.S == 1 ? tsweep_blocks(g, sizeof(T) == 8) : msweep_blocks<T>(g, L.S);
       if (L.S == 1 && has_next && nextL.S == 1) {
         pend_m = L.m;
         pend_parts = parts;
@@ -1443,7 +1452,9 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->steps_done = 0;
   h->resident = resident_fits(h);
   h->tag = 1;
-  h->sweeps_per_launch = cfg->sweeps_per_launch > 0 ? cfg->sweeps_per_launch : kDefaultSweepsPerLaunch;
+  const int depth = cfg->precision == LES_FP64 ? msweep_depth<double>(h->grid)
+                                               : msweep_depth<float>(h->grid);
+  h->sweeps_per_launch = cfg->sweeps_per_launch > 0 ? cfg->sweeps_per_launch : depth;
 
   auto cleanup = [&](int code) {
     les_destroy(h);

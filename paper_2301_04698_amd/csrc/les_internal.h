@@ -78,13 +78,17 @@ constexpr int kBlock = 256;          // threads per block of elementwise kernels
 constexpr int kReduceBlocks = 1024;  // fixed grid of the generic reductions
 constexpr int kPartials = 1 << 16;   // max partials of one reduction (sweep tiles)
 
-// Temporally blocked Poisson sweeps: up to kMaxSweepsPerLaunch sweeps per
-// launch (kDefaultSweepsPerLaunch unless the configuration asks otherwise).
+// Sweeps per launch that a configuration may ask for.
 constexpr int kMaxSweepsPerLaunch = 2;
-constexpr int kDefaultSweepsPerLaunch = 1;
 
-// Blocks of a tsweep launch of S sweeps (its count of residual partials).
-int tsweep_blocks(const Grid &g, int S, bool is_double);
+// Blocks of a launch of one sweep and of S sweeps (its count of residual
+// partials).
+int tsweep_blocks(const Grid &g, bool is_double);
+template <typename T>
+int msweep_blocks(const Grid &g, int S);
+// Sweeps per launch of a solve launch by launch.
+template <typename T>
+int msweep_depth(const Grid &g);
 
 // ------------------------------------------------------------ launchers
 template <typename T>
@@ -184,19 +188,24 @@ void launch_ctl_budget(SolveCtl *ctl, int max_sweeps, hipStream_t s);
 template <typename T>
 void launch_zero(const Grid &g, T *f, hipStream_t s);
 
-// S sweeps from (prev, cur) = (phi_{m-1}, phi_m) giving out_prev = phi_{m+S-1}
-// (S >= 2, Chebyshev) and out_last = phi_{m+S}; check: FP64 partial sums of
-// the residual of cur, one per block (tsweep_blocks of them).  first: sweep
-// m is the first of the solve.  omega_cheb: S weights of sweeps m .. m+S-1.
-// dec_m >= 0 (S == 1 only): block 0 also reduces the dec_np partials of an
-// earlier checking launch of sweep dec_m and applies its stopping decision
-// to ctl.  Outputs never alias inputs.
+// One sweep from (prev, cur) = (phi_{m-1}, phi_m) giving out = phi_{m+1};
+// check: FP64 partial sums of the residual of cur, one per block
+// (tsweep_blocks of them).  first: sweep m is the first of the solve.
+// dec_m >= 0: block 0 also reduces the dec_np partials of an earlier checking
+// launch of sweep dec_m and applies its stopping decision to ctl.  Outputs
+// never alias inputs.
 template <typename T>
-void launch_tsweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
-                   double omega_jacobi, const double *omega_cheb, const T *cur, const T *prev,
-                   T *out_last, T *out_prev, const T *rhs, SolveCtl *ctl, double *partials,
-                   const double *dec_partials, int dec_np, int dec_m, int64_t *snap,
-                   int snap_seq, hipStream_t s);
+void launch_tsweep(const Grid &g, bool chebyshev, bool check, bool first, double omega_jacobi,
+                   double omega_cheb, const T *cur, const T *prev, T *out, const T *rhs,
+                   SolveCtl *ctl, double *partials, const double *dec_partials, int dec_np,
+                   int dec_m, int64_t *snap, int snap_seq, hipStream_t s);
+// S = 2 or 3 sweeps at once: out_prev = phi_{m+S-1} (Chebyshev) and out_last
+// = phi_{m+S}; omega_cheb: the S weights; otherwise as above (msweep_blocks
+// partials).
+template <typename T>
+void launch_msweep(const Grid &g, int S, bool chebyshev, bool check, bool first, double omega_jacobi,
+                   const double *omega_cheb, const T *cur, const T *prev, T *out_last, T *out_prev,
+                   const T *rhs, SolveCtl *ctl, double *partials, hipStream_t s);
 
 // Whole solves resident on the chip (les_resident.h).  psweep_blocks: blocks
 // of such a launch, 0 where the grid does not fit; at most kResidentBlocks,
