@@ -54,6 +54,7 @@ struct Layout {
   size_t partials2; // kPartials doubles: every other residual check's partials
   size_t ctl;       // SolveCtl
   size_t diag;      // nz x kDiagStride doubles
+  size_t diag_parts;  // what they are summed from
   size_t hist;      // n_subiter fields: previous step's solutions (history guess)
   // learned guess: residual (FP32), network input (bf16), two 16-channel
   // activations (bf16), parameters (FP32) and their bf16 copy, scales
@@ -188,6 +189,8 @@ Layout layout_of(const les_config *c) {
   off = align_up(off + sizeof(SolveCtl));
   L.diag = off;
   off = align_up(off + (size_t)c->nz * kDiagStride * sizeof(double));
+  L.diag_parts = off;
+  off = align_up(off + diag_part_values(grid_of(c)) * sizeof(double));
   L.hist = off;  // LES_GUESS_LEARNED3: one field, the extrapolated base
   if (uses_hist(c)) off = align_up(off + (size_t)c->n_subiter * n * es);
   else if (c->guess == LES_GUESS_LEARNED3) off = align_up(off + n * es);
@@ -1224,8 +1227,8 @@ int diag_impl(les_handle *h, les_diag *out, double *profiles) {
   const int nz = g.nz;
   launch_thermo<T>(g, h->thermo, V.P, V.thl, V.qt, nullptr, nullptr, nullptr, nullptr,
                    V.f[F_B_M], V.f[F_QL_M], nullptr, nullptr, h->stream);
-  launch_diag<T>(g, V.dyn, V.P, V.u, V.v, V.w, V.thl, V.qt, V.f[F_QL_M], V.f[F_B_M], V.diag,
-                 h->stream);
+  launch_diag<T>(g, V.P, V.u, V.v, V.w, V.thl, V.qt, V.f[F_QL_M], V.f[F_B_M],
+                 (double *)ws(h, h->lay.diag_parts), V.diag, h->stream);
   LAUNCH_TRY();
   HIP_TRY(hipMemcpyAsync(h->diag_host, V.diag, (size_t)nz * kDiagStride * sizeof(double),
                          hipMemcpyDeviceToHost, h->stream));

@@ -296,10 +296,12 @@ void launch_ctl_reset(SolveCtl *ctl, int max_sweeps, int fixed, hipStream_t s);
 // Per-level FP64 sums for the diagnostics: level_sums[k*kDiagStride + m],
 // m = 0..8 horizontal sums of thl, qt, ql, u, v, w, w^2, w^3, b; 9 sum rho0 thl,
 // 10 sum rho0 qt, 11 sum rho0 |u|^2/2, 12 sum div^2, 13 max |div|, 14 max CFL.
+// parts: diag_part_values(g) doubles.
 constexpr int kDiagStride = 16;
+size_t diag_part_values(const Grid &g);
 template <typename T>
-void launch_diag(const Grid &g, const Dyn<T> &d, const Profiles<T> &P, const T *u, const T *v,
-                 const T *w, const T *thl, const T *qt, const T *ql, const T *b,
+void launch_diag(const Grid &g, const Profiles<T> &P, const T *u, const T *v, const T *w,
+                 const T *thl, const T *qt, const T *ql, const T *b, double *parts,
                  double *level_sums, hipStream_t s);
 
 }  // namespace lesmi
