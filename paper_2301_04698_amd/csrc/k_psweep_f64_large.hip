@@ -4,8 +4,8 @@
 namespace lesmi {
 namespace resident {
 
-LES_RESIDENT(Shapes<double>::L, true, true)
-LES_RESIDENT(Shapes<double>::L, true, false)
+LES_RESIDENT(Shapes<double>::M3, true, true)
+LES_RESIDENT(Shapes<double>::M3, true, false)
 
 }  // namespace resident
 }  // namespace lesmi

@@ -701,6 +701,11 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
       __syncthreads();
       publish_xy(gc, t + 1);
       if constexpr (NG == 1) {
+        // A face just published takes most of a microsecond to be seen, and a
+        // read that comes too early costs a whole round trip more.  Pauses of
+        // 0, 0.1, 0.2, 0.3, 0.4 us: 1.82, 1.74, 1.70, 1.79, 1.90 us per sweep
+        // at 64 x 64 x 64 FP32.
+        __builtin_amdgcn_s_sleep(8);
         issue(gn, tn);
         collect(gn, tn, pp ^ 1);
         __syncthreads();
@@ -802,13 +807,17 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
   }
 }
 
-// Box shapes by storage type (FP64: half the cells per thread).
+// Box shapes, 2048 to 32768 cells (64 x 8 x 4 to 64 x 16 x 32; one row 64 x 32
+// or 64 x 256); FP64 fills the registers at half of that.
 template <typename T>
 struct Shapes {
-  static constexpr int F = sizeof(T) == 4 ? 1 : 2;
-  using L = Box<T, 2, 32 / F, 4 / F, false, 1>;
-  using M = Box<T, 2, 8 / F, 4 / F, false, 4>;
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int G = F32 ? 4 : 2;  // levels per group
   using S = Box<T, 1, 4, 4, false, 1>;
+  using M1 = Box<T, 2, 4, G, false, F32 ? 2 : 4>;
+  using M2 = Box<T, 2, 8, G, false, F32 ? 4 : 1>;
+  using M3 = Box<T, 2, 16, G, false, 1>;
+  using L = std::conditional_t<F32, Box<T, 2, 32, G, false, 1>, M3>;
   using RowL = Box<T, 1, 32, 4, true, 4>;
   using RowS = Box<T, 1, 4, 4, true, 1>;
 };

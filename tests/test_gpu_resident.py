@@ -21,12 +21,13 @@ def gpu():
 
 
 # (nz, ny, nx): small boxes hold 64 x 8 x 4 cells (one row: 64 x 1 x 32),
-# medium ones 64 x 16 x 8 (FP64: x 4), large ones 64 x 32 x 16 (FP64: x 8;
-# one row: 64 x 1 x 256), at most 256 boxes of a shape
+# medium ones 64 x 16 x 4 and x 8, large ones 64 x 16 x 16 and, in FP32, x 32
+# (one row: 64 x 1 x 256), at most 256 boxes of a shape
 SMALL = [(4, 8, 64), (8, 16, 128), (4, 2, 2), (5, 3, 3), (33, 20, 130), (32, 32, 32), (7, 9, 65),
          (61, 75, 100)]
-MEDIUM = [(64, 128, 256), (50, 90, 150)]
-LARGE = {"fp32": [(128, 256, 256), (100, 200, 250), (120, 33, 1000)],
+MEDIUM = [(64, 128, 256), (50, 90, 150), (50, 120, 250), (16, 256, 256)]
+LARGE = {"fp32": [(128, 256, 256), (100, 200, 250), (120, 33, 1000), (64, 256, 256),
+                  (100, 120, 250)],
          "fp64": [(64, 256, 256), (70, 130, 200)]}
 ROWS = [(32, 1, 64), (8, 1, 2), (9, 1, 65), (128, 1, 1024), (256, 1, 256), (250, 1, 2100),
         (640, 1, 5120)]
