@@ -31,8 +31,8 @@ bool try_box(const Grid &g, int shape, Fit *f) {
 }
 
 // The smallest shape whose boxes all fit, so that a grid spreads over many
-// CUs: 128 x 128 x 64 FP32 takes 3.4 us per sweep in 64 boxes of M2 and 2.8 in
-// 128 of M1, 256 x 128 x 64 FP64 10.3 in 64 of M3 and 7.5 in 128 of M2.
+// CUs: 128 x 128 x 64 FP32 takes 3.4 us per sweep in 128 boxes of M2 and 2.5 in
+// 256 of M1, 256 x 128 x 64 FP64 10.2 in 128 of M3 and 7.0 in 256 of M2.
 // Fixed-weight Jacobi sweeps (small grids: their count grows with the square
 // of the grid's width) have no large boxes.
 template <typename T>
@@ -91,15 +91,15 @@ hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double r
                       : launch_box<typename S::B, true, false>(a, f.nb, s))   \
              : (f.rag ? launch_box<typename S::B, false, true>(a, f.nb, s)    \
                       : launch_box<typename S::B, false, false>(a, f.nb, s)))
-#define LES_CHEB(B)                                          \
-  (f.rag ? launch_box<typename S::B, true, true>(a, f.nb, s) \
+#define LES_CHEB(B, RAGGED)                                       \
+  (f.rag ? launch_box<typename S::RAGGED, true, true>(a, f.nb, s) \
          : launch_box<typename S::B, true, false>(a, f.nb, s))
   switch (f.shape) {
     case 1: return LES_BOX(S);
     case 2: return LES_BOX(M1);
     case 3: return LES_BOX(M2);
-    case 4: return LES_CHEB(M3);
-    case 5: return LES_CHEB(L);
+    case 4: return LES_CHEB(M3, M3Rag);
+    case 5: return LES_CHEB(L, LRag);
     case 6: return LES_BOX(RowS);
     case 7: return LES_BOX(RowL);
     default: return hipErrorInvalidValue;

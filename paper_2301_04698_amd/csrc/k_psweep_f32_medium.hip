@@ -8,7 +8,7 @@ LES_RESIDENT(Shapes<float>::M2, true, true)
 LES_RESIDENT(Shapes<float>::M2, true, false)
 LES_RESIDENT(Shapes<float>::M2, false, true)
 LES_RESIDENT(Shapes<float>::M2, false, false)
-LES_RESIDENT(Shapes<float>::M3, true, true)
+LES_RESIDENT(Shapes<float>::M3Rag, true, true)
 LES_RESIDENT(Shapes<float>::M3, true, false)
 
 }  // namespace resident

@@ -4,7 +4,7 @@
 namespace lesmi {
 namespace resident {
 
-LES_RESIDENT(Shapes<double>::M3, true, true)
+LES_RESIDENT(Shapes<double>::M3Rag, true, true)
 LES_RESIDENT(Shapes<double>::M3, true, false)
 
 }  // namespace resident

@@ -9,14 +9,14 @@
 // only the faces of the boxes move, through memory, once per sweep.  One
 // launch runs every sweep of a solve and takes the stopping decision itself.
 //
-// What bounds it: FP64 issue where the boxes are large (a cell's update is 14
-// FP64 instructions at 2.2 ns per wave and SIMD: 6.6 of the 11.4 us below;
-// without the exchange it runs 8.6 us, without waiting for it 10.0), the
-// round trip of a face through memory (about 1.7 us) where they are small.
+// What bounds it: FP64 issue where the boxes are large (a cell's update is 19
+// FP64 instructions and conversions at 2.2 ns per wave and SIMD: 5.4 of the
+// 10.5 us below, the rest other instructions, barriers and waits for faces),
+// the round trip of a face through memory (about 1.5 us) where they are small.
 // Microseconds per sweep, one-sweep kernel and here: 256 x 256 x 128 FP32
-// 22.9 and 11.4; 256 x 256 x 64 FP64 24.2 and 11.7; 64 x 64 x 64 FP32 5.1 and
-// 1.8; 250 x 200 x 100 FP32 (ragged boxes) 17.5 and 13.1; one row, 1024 x 128
-// FP64 4.6 and 1.8.
+// 22.9 and 10.5; 256 x 256 x 64 FP64 24.2 and 11.7; 64 x 64 x 64 FP32 5.1 and
+// 1.7; 250 x 200 x 100 FP32 (ragged boxes) 17.5 and 11; one row, 1024 x 128
+// FP64 4.6 and 1.7.
 //
 // Layout.  A block is eight waves; lane = x (64 cells), a thread holds R rows
 // by Z levels of its x.  Waves stack in y (three-dimensional grids: boxes of
@@ -75,6 +75,10 @@ struct Box {
   // y faces go to memory by way of LDS, a word per thread, where several
   // groups hide the longer way; from the edge waves at once otherwise
   static constexpr bool YLDS = NG >= 4;
+  // the largest boxes with long groups have LDS for one group's rows only: a
+  // second barrier per group instead of a second buffer
+  static constexpr bool SB = NV * GL * sizeof(T_) >= 256 && GL * sizeof(T_) > 16;
+  static constexpr int NB = SB ? 1 : 2;
   static constexpr int SL = 8 / (int)sizeof(T_);  // levels per LDS operand read
   // face words of one parity: z faces [slot][lane], y faces [level][lane],
   // x faces [slot][level]; x level index is the thread's own
@@ -177,12 +181,13 @@ struct Shared {
   using V = Vec<T, B::GL>;
   V rhs[B::NV > B::RV ? B::NV - B::RV : 1][kNT];
   // first row of each wave but the first and last row of each but the last,
-  // in the group at hand and the next (three-dimensional boxes)
-  V lo[2][B::D2 ? 1 : kNW - 1][64], hi[2][B::D2 ? 1 : kNW - 1][64];
+  // in the group at hand and (not SB) the next (three-dimensional boxes)
+  V lo[B::NB][B::D2 ? 1 : kNW - 1][64], hi[B::NB][B::D2 ? 1 : kNW - 1][64];
   // lowest and highest level of each wave, by iterate parity (one-row boxes)
   T zlo[2][B::D2 ? kNW : 1][B::D2 ? 64 : 1], zhi[2][B::D2 ? kNW : 1][B::D2 ? 64 : 1];
   // y and x faces of the group at hand and the next, and those to publish
-  V yh[2][2][B::D2 ? 1 : 64], xh[2][2][B::NS], ypub[2][2][B::YLDS && !B::D2 ? 64 : 1], xpub[2][2][B::NS];
+  V yh[2][2][B::D2 ? 1 : 64], xh[2][2][B::NS];
+  V ypub[B::NB][2][B::YLDS && !B::D2 ? 64 : 1], xpub[B::NB][2][B::NS];
   double red[kNW];
   double total;
   int dead;
@@ -447,6 +452,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
 
   double acc[R], wc = 1.0;  // residual sum of each row
   int pp = 0;  // LDS slot of the faces of the group at hand
+  constexpr bool kOne = B::SB;
 
   // ---- one group of sweep m: Cur = phi_m (tag t), Nxt = phi_{m-1} in,
   // phi_{m+1} out
@@ -457,9 +463,10 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
     // LDS operands, SL levels at a time
     constexpr int SL = B::SL, RV = B::RV;
     using P = Vec<T, SL>;
-    const P *const plo = (const P *)(wv == 0 || B::D2 ? &sh.yh[pp][0][ln] : &sh.hi[pp][wv - 1][ln]);
+    const int rp = kOne ? 0 : pp;
+    const P *const plo = (const P *)(wv == 0 || B::D2 ? &sh.yh[pp][0][ln] : &sh.hi[rp][wv - 1][ln]);
     const P *const phi = (const P *)(wv == last || B::D2 ? &sh.yh[pp][1][ln]
-                                                         : &sh.lo[pp][min(wv, kNW - 2)][ln]);
+                                                         : &sh.lo[rp][min(wv, kNW - 2)][ln]);
     const P *const px = (const P *)&sh.xh[pp][ln == 0 ? 0 : 1][wv * R];
     P ylo, yhi, xe[R], rv[R];
     double c[R], b[R];
@@ -598,14 +605,14 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
           static_for<GL>([&](auto qc) __attribute__((always_inline)) {
             v.v[qc] = Nxt[0][K0 + decltype(qc)::value];
           });
-          sh.ypub[pp][0][ln] = v;
+          sh.ypub[kOne ? 0 : pp][0][ln] = v;
         }
         if (wv == last) {
           static_for<GL>([&](auto qc) __attribute__((always_inline)) {
             constexpr int k = K0 + decltype(qc)::value;
             v.v[qc] = last_row(std::integral_constant<int, k>{}, Nxt);
           });
-          sh.ypub[pp][1][ln] = v;
+          sh.ypub[kOne ? 0 : pp][1][ln] = v;
         }
       } else {
         if (wv == 0)
@@ -626,7 +633,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
         static_for<GL>([&](auto qc) __attribute__((always_inline)) {
           v.v[qc] = Nxt[rc][K0 + decltype(qc)::value];
         });
-        sh.xpub[pp][ln == 0 ? 0 : 1][wv * R + rc] = v;
+        sh.xpub[kOne ? 0 : pp][ln == 0 ? 0 : 1][wv * R + rc] = v;
       });
   };
   // after the barrier: the x and y faces from LDS
@@ -640,7 +647,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
         const int e = q * kNT + wv * 64 + ln;
         const int h = e % NWD, c = e / NWD % 64, l = e / (64 * NWD) % GL, side = e / (64 * NWD * GL);
         const uint32_t v =
-            ((const uint32_t *)&sh.ypub[pp][0][0].v[0])[((side * 64 + c) * GL + l) * NWD + h];
+            ((const uint32_t *)&sh.ypub[kOne ? 0 : pp][0][0].v[0])[((side * 64 + c) * GL + l) * NWD + h];
         int us;
         const int o = y_run(q, &us);
         put_word(Word{a.faces, (to + (us ? oYhi : oYlo) + gi * GL * 64 * NWD + o) * 8u + lane8()}, v,
@@ -653,7 +660,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
         const int o = x_run(q, &side);
         const uint32_t at = to + (side ? oXhi : oXlo) + gi * (B::XN / 2) + o;
         const int e = min(q * kNT + wv * 64 + ln, B::XN - 1);
-        const uint32_t v = ((const uint32_t *)&sh.xpub[pp][0][0].v[0])[e];
+        const uint32_t v = ((const uint32_t *)&sh.xpub[kOne ? 0 : pp][0][0].v[0])[e];
         put_word(Word{a.faces, at * 8u + (kXRuns ? lane8() : 0u)}, v, t);
       }
   };
@@ -666,12 +673,12 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
       static_for<GL>([&](auto qc) __attribute__((always_inline)) {
         v.v[qc] = F[0][K0 + decltype(qc)::value];
       });
-      if (wv > 0) sh.lo[pp ^ 1][wv > 0 ? wv - 1 : 0][ln] = v;
+      if (wv > 0) sh.lo[kOne ? 0 : pp ^ 1][wv > 0 ? wv - 1 : 0][ln] = v;
       static_for<GL>([&](auto qc) __attribute__((always_inline)) {
         constexpr int k = K0 + decltype(qc)::value;
         v.v[qc] = last_row(std::integral_constant<int, k>{}, F);
       });
-      if (wv < kNW - 1) sh.hi[pp ^ 1][wv < kNW - 1 ? wv : 0][ln] = v;
+      if (wv < kNW - 1) sh.hi[kOne ? 0 : pp ^ 1][wv < kNW - 1 ? wv : 0][ln] = v;
     }
   };
   // a whole sweep m
@@ -693,13 +700,15 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
       if (NG > 1 && take) issue(gn, tn);
       compute(gc, Cur, Nxt, t);
       publish(gc, Nxt, t + 1);
-      pass_rows(std::integral_constant<int, gn>{}, wraps ? Nxt : Cur);
+      if (!B::SB) pass_rows(std::integral_constant<int, gn>{}, wraps ? Nxt : Cur);
       if (NG > 1) {
         if (take) collect(gn, tn, pp ^ 1);
         else start_levels(gn);
       }
       __syncthreads();
+      if (B::SB) pass_rows(std::integral_constant<int, gn>{}, wraps ? Nxt : Cur);
       publish_xy(gc, t + 1);
+      if (B::SB) __syncthreads();
       if constexpr (NG == 1) {
         // A face just published takes most of a microsecond to be seen, and a
         // read that comes too early costs a whole round trip more.  Pauses of
@@ -808,16 +817,25 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
 }
 
 // Box shapes, 2048 to 32768 cells (64 x 8 x 4 to 64 x 16 x 32; one row 64 x 32
-// or 64 x 256); FP64 fills the registers at half of that.
+// or 64 x 256); FP64 fills the registers at half of that.  FP64 takes one row
+// per thread where it can: every thread reads the z faces of its rows, two
+// words a value.  Longer groups mean fewer exchanges: 8 levels instead of 4
+// took 256 x 256 x 64 FP32 from 6.2 to 4.9 us per sweep, 256 x 256 x 128 from
+// 11.4 to 10.5 and 250 x 200 x 100 (ragged boxes) from 13.1 to 11; 4 instead of
+// 2 the ragged largest FP64 boxes (250 x 200 x 60) from 12.4 to 10.8 but the
+// full ones (256 x 256 x 64) from 11.7 to 12.4.  64 x 8 x 8 boxes instead of 64
+// x 16 x 4 took 128 x 128 x 64 FP64 from 7.3 to 5.8, 64 x 8 x 16 instead of 64 x
+// 16 x 8 200 x 120 x 60 from 8.4 to 6.2.
 template <typename T>
 struct Shapes {
   static constexpr bool F32 = sizeof(T) == 4;
-  static constexpr int G = F32 ? 4 : 2;  // levels per group
   using S = Box<T, 1, 4, 4, false, 1>;
-  using M1 = Box<T, 2, 4, G, false, F32 ? 2 : 4>;
-  using M2 = Box<T, 2, 8, G, false, F32 ? 4 : 1>;
-  using M3 = Box<T, 2, 16, G, false, 1>;
-  using L = std::conditional_t<F32, Box<T, 2, 32, G, false, 1>, M3>;
+  using M1 = Box<T, 1, 8, F32 ? 8 : 4, false, 2>;
+  using M2 = std::conditional_t<F32, Box<T, 2, 8, 8, false, 2>, Box<T, 1, 16, 4, false, 1>>;
+  using M3 = Box<T, 2, 16, F32 ? 8 : 2, false, 1>;
+  using M3Rag = Box<T, 2, 16, F32 ? 8 : 4, false, 1>;
+  using L = std::conditional_t<F32, Box<T, 2, 32, 8, false, 1>, M3>;  // FP32 only
+  using LRag = std::conditional_t<F32, L, M3Rag>;
   using RowL = Box<T, 1, 32, 4, true, 4>;
   using RowS = Box<T, 1, 4, 4, true, 1>;
 };
