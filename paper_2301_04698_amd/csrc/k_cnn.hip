@@ -11,6 +11,7 @@
 // over pairs of in-plane taps (16 consecutive output cells per product),
 // the C -> 16 layer as one GEMM over (tap, channel) pairs.  The backward
 // pass is FP32 vector code (FP64 sums in the weight gradient).
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -96,18 +97,20 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const float *__restrict__ 
   if (q < n) wbf[q] = f2bf(params[q]);
 }
 
-// One thread per (cell, channel) of the channels-last output.
-__global__ __launch_bounds__(kBlock) void round_kernel(int64_t n, int C, int64_t cells,
-                                                       const float *__restrict__ x,
+// One thread per cell of batch item blockIdx.y: its C channels.
+template <int C>
+__global__ __launch_bounds__(kBlock) void round_kernel(int64_t cells, const float *__restrict__ x,
                                                        const double *__restrict__ scale,
                                                        uint16_t *__restrict__ a0) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n * C) return;
-  const int c = (int)(q % C);
-  const int64_t cell = q / C, b = cell / cells, r = cell - b * cells;
-  const float xv = x[(b * C + c) * cells + r];
-  const float v = scale ? (float)((double)xv * *scale) : xv;
-  a0[q] = f2bf(v);
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= cells) return;
+  const int64_t b = blockIdx.y;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const float xv = x[(b * C + c) * cells + r];
+    const float v = scale ? (float)((double)xv * *scale) : xv;
+    a0[(b * cells + r) * C + c] = f2bf(v);
+  }
 }
 
 // Layers 1, 2 (16 -> 16) and 3 (16 -> 1) on the matrix cores as implicit
@@ -540,8 +543,13 @@ __global__ __launch_bounds__(256, 2) void conv_mid_kernel(
 // Layer 0 (CI -> 16) on the matrix cores: D(out ch x 16 cells) = W(out ch x
 // K) X(K x 16 cells) over the K = 27 CI (tap, channel) pairs, k = tap CI +
 // c, padded to a multiple of 16; the im2col operand is gathered from a
-// three-plane LDS ring of bfloat16 inputs (channel planes side by side);
-// 27 CI / 16 MFMAs (rounded up) per 16 cells.
+// four-slot LDS ring of bfloat16 input planes, channels last (one barrier per
+// plane); 27 CI / 16 MFMAs (rounded up) per 16 cells.  A lane's pairs are its
+// own, so its offsets in the ring are made once; a plane adds its slot and
+// wraps with a mask (ring and slots are powers of two).
+// Bound by the LDS gathers.  200 x 160 x 64, three channels: 61 us with the
+// addresses made anew for every value, 40 us here; 16 crops of 42 x 42 x 128,
+// one channel: 46 and 33 us.
 template <int CI>
 __global__ __launch_bounds__(256) void conv_in_kernel(CnnGeom G, const uint16_t *__restrict__ ain,
                                                       const float *__restrict__ params,
@@ -549,83 +557,96 @@ __global__ __launch_bounds__(256) void conv_in_kernel(CnnGeom G, const uint16_t 
                                                       float alpha, uint16_t *__restrict__ aout,
                                                       CnnTiling C) {
   constexpr int K = kCnnTaps * CI, KM = (K + 15) / 16;
-  __shared__ uint16_t lds[3][CI][kCnnPlane];
+  constexpr uint32_t kSlotB = CI == 1 ? 1024 : 4096, kRingB = 4 * kSlotB;
+  static_assert(kCnnPlane * CI * 2 <= kSlotB, "a plane fits its slot");
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kRingB];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int row = lane & 15, quad = lane >> 4;
   const CnnTile T = cnn_tile(G, C);
   if (!T.valid) return;  // the whole block
-  // A operands: W0[tap][o = row][c] for k = 16 m + 4 quad + r
+  // A operands: W0[tap][o = row][c] for k = 16 m + 4 quad + r; the value's
+  // offset in the ring, for plane 0 and the wave's first 16 cells
   bf16x4 wa[KM];
+  uint32_t off[KM][4];
 #pragma unroll
   for (int m = 0; m < KM; ++m)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int kk = 16 * m + 4 * quad + r;
       wa[m][r] = kk < K ? (short)wbf[((kk / CI) * kCnnCh + row) * CI + kk % CI] : (short)0;
+      const int kc = min(kk, K - 1), tap = kc / CI, c = kc % CI;
+      const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
+      off[m][r] = (uint32_t)dz * kSlotB +
+                  (uint32_t)((((wv + 1 + dy) * kCnnPX + row + 1 + dx) * CI + c) * 2);
     }
   float bq[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) bq[r] = params[cnn_bias_offset(CI, 0) + 4 * quad + r];
-  // plane kk (mirror-clamped) fetched into registers one plane ahead
+  // plane kk (mirror-clamped) fetched into registers one plane ahead (the
+  // loads past the plane repeat its last value and are not stored)
   constexpr int kLoads = (kCnnPlane * CI + 255) / 256;
   uint16_t pre[kLoads];
-  auto fetch = [&](int kk) {
+  int32_t src[kLoads];
 #pragma unroll
-    for (int u = 0; u < kLoads; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      if (e < kCnnPlane * CI) {
-        const int cell = e / CI, c = e - cell * CI;
-        const int ly = cell / kCnnPX, lx = cell - ly * kCnnPX;
-        pre[u] = ain[cnn_src(G, T, kk, ly, lx) * CI + c];
-      }
-    }
+  for (int u = 0; u < kLoads; ++u) {
+    const int e = min((int)threadIdx.x + 256 * u, kCnnPlane * CI - 1);
+    const int cell = e / CI, c = e - cell * CI;
+    const int ly = cell / kCnnPX, lx = cell - ly * kCnnPX;
+    const CnnTile T0 = {0, T.ox0, T.oy0, T.ix0, T.iy0, 0, 0, true};
+    src[u] = (int32_t)cnn_src(G, T0, 0, ly, lx) * CI + c;
+  }
+  const int64_t plane = (int64_t)G.nyi * G.nxi * CI;
+  auto fetch = [&](int kk) __attribute__((always_inline)) {
+    const uint16_t *in = ain + ((int64_t)T.b * G.nz + min(max(kk, 0), G.nz - 1)) * plane;
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) pre[u] = in[src[u]];
   };
-  auto store = [&](int slot) {
+  auto store = [&](int kk) __attribute__((always_inline)) {
+    unsigned char *slot = lds + (uint32_t)(kk & 3) * kSlotB;
 #pragma unroll
     for (int u = 0; u < kLoads; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      if (e < kCnnPlane * CI) {
-        const int cell = e / CI, c = e - cell * CI;
-        lds[slot][c][cell] = pre[u];
-      }
+      const int e = (int)threadIdx.x + 256 * u;
+      if (e < kCnnPlane * CI) *(uint16_t *)(slot + 2 * e) = pre[u];
     }
   };
   fetch(T.k0 - 1);
-  store((T.k0 + 2) % 3);
+  store(T.k0 - 1);
   fetch(T.k0);
-  store(T.k0 % 3);
+  store(T.k0);
   fetch(T.k0 + 1);
   const int oy = T.oy0 + wv;
   for (int k = T.k0; k < T.k1; ++k) {
-    __syncthreads();
-    store((k + 1) % 3);
+    // the slot of plane k + 1 was last read two planes ago
+    store(k + 1);
     __syncthreads();
     if (k + 1 < T.k1) fetch(k + 2);
+    floatx4 acc[4];
 #pragma unroll
-    for (int t4 = 0; t4 < 4; ++t4) {
-      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int t4 = 0; t4 < 4; ++t4) acc[t4] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int m = 0; m < KM; ++m) {
+    for (int m = 0; m < KM; ++m) {
+      uint32_t at[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) at[r] = ((uint32_t)k * kSlotB + off[m][r]) & (kRingB - 1);
+#pragma unroll
+      for (int t4 = 0; t4 < 4; ++t4) {
         bf16x4 xb;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int kk = 16 * m + 4 * quad + r;
-          short v = 0;
-          if (kk < K) {
-            const int tap = kk / CI, c = kk % CI;
-            const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-            v = (short)lds[(k + dz + 3) % 3][c][(wv + 1 + dy) * kCnnPX + 16 * t4 + row + 1 + dx];
-          }
-          xb[r] = v;
+          xb[r] = *(const short *)(lds + at[r] + 16 * t4 * CI * 2);
+          if (16 * m + 12 + r >= K && 16 * m + 4 * quad + r >= K) xb[r] = 0;
         }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[m], xb, acc, 0, 0, 0);
+        acc[t4] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa[m], xb, acc[t4], 0, 0, 0);
       }
+    }
+#pragma unroll
+    for (int t4 = 0; t4 < 4; ++t4) {
       const int ox = T.ox0 + 16 * t4 + row;
       if (oy < G.nyo && ox < G.nxo) {
-        const uint32_t lo = f2bf2(leaky(acc[0] + bq[0], alpha),
-                                  leaky(acc[1] + bq[1], alpha));
-        const uint32_t hi = f2bf2(leaky(acc[2] + bq[2], alpha),
-                                  leaky(acc[3] + bq[3], alpha));
+        const uint32_t lo = f2bf2(leaky(acc[t4][0] + bq[0], alpha),
+                                  leaky(acc[t4][1] + bq[1], alpha));
+        const uint32_t hi = f2bf2(leaky(acc[t4][2] + bq[2], alpha),
+                                  leaky(acc[t4][3] + bq[3], alpha));
         const int64_t q = (((int64_t)T.b * G.nz + k) * G.nyo + oy) * G.nxo + ox;
         *(uint2 *)(aout + q * kCnnCh + 4 * quad) = make_uint2(lo, hi);
       }
@@ -1513,7 +1534,16 @@ void launch_cnn_pack(const float *params, int n, uint16_t *wbf, hipStream_t s) {
 
 void launch_cnn_round(int64_t n, int C, int64_t cells, const float *x, const double *scale,
                       uint16_t *a0, hipStream_t s) {
-  round_kernel<<<blocks_for(n * C), kBlock, 0, s>>>(n, C, cells, x, scale, a0);
+  // at most 65535 batch items a launch
+  for (int64_t b = 0, batch = n / cells; b < batch; b += 65535) {
+    const dim3 grid(blocks_for(cells), (unsigned)std::min<int64_t>(batch - b, 65535));
+    const float *xb = x + b * C * cells;
+    uint16_t *ab = a0 + b * C * cells;
+    if (C == 1)
+      round_kernel<1><<<grid, kBlock, 0, s>>>(cells, xb, scale, ab);
+    else
+      round_kernel<3><<<grid, kBlock, 0, s>>>(cells, xb, scale, ab);
+  }
 }
 
 void launch_cnn_conv(int layer, const CnnGeom &G, const uint16_t *ain, const float *params,
