@@ -284,7 +284,9 @@ int msweep_blocks(const Grid &g, int S) {
 // 2500 x 4 FP32) 58 and 39; 2.7 (2120 x 16 x 640 FP64) 155 and 83; 7.2 (1000 x
 // 33 x 44 FP32) 6.8 and 6.9; 10.4 (5120 x 8 x 640 FP32) 86 and 195.
 template <typename T>
-int msweep_depth(const Grid &g) {
+int msweep_depth(const Grid &g, int asked) {
+  if (asked > 1) return msweep_blocks<T>(g, asked) <= kPartials ? asked : 1;
+  if (asked == 1) return 1;
   constexpr int S = 3, BY = MTile<T>::BY;
   const MShape m = mshape_of(g, S, BY);
   const int64_t rounds = (m.ntiles + 255) / 256;
@@ -328,7 +330,7 @@ void launch_msweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
 
 #define LES_INST(T)                                                                              \
   template int msweep_blocks<T>(const Grid &, int);                                              \
-  template int msweep_depth<T>(const Grid &);                                                    \
+  template int msweep_depth<T>(const Grid &, int);                                               \
   template void launch_msweep<T>(const Grid &, int, bool, bool, bool, double, const double *,    \
                                  const T *, const T *, T *, T *, const T *, SolveCtl *, double *, \
                                  hipStream_t);

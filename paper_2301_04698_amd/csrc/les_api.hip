@@ -1455,9 +1455,9 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->steps_done = 0;
   h->resident = resident_fits(h);
   h->tag = 1;
-  const int depth = cfg->precision == LES_FP64 ? msweep_depth<double>(h->grid)
-                                               : msweep_depth<float>(h->grid);
-  h->sweeps_per_launch = cfg->sweeps_per_launch > 0 ? cfg->sweeps_per_launch : depth;
+  h->sweeps_per_launch = cfg->precision == LES_FP64
+                             ? msweep_depth<double>(h->grid, cfg->sweeps_per_launch)
+                             : msweep_depth<float>(h->grid, cfg->sweeps_per_launch);
 
   auto cleanup = [&](int code) {
     les_destroy(h);

@@ -86,9 +86,10 @@ constexpr int kMaxSweepsPerLaunch = 2;
 int tsweep_blocks(const Grid &g, bool is_double);
 template <typename T>
 int msweep_blocks(const Grid &g, int S);
-// Sweeps per launch of a solve launch by launch.
+// Sweeps per launch of a solve launch by launch: what the configuration asks
+// for (where a launch's residual partials fit), or the kernel's own choice (0).
 template <typename T>
-int msweep_depth(const Grid &g);
+int msweep_depth(const Grid &g, int asked);
 
 // ------------------------------------------------------------ launchers
 template <typename T>

@@ -114,3 +114,38 @@ def test_resident_solve_with_a_guess_bitwise_equal(gpu, precision, mean_mode):
         assert np.array_equal(a[0], b[0])
         assert a[1] == b[1]
         assert b[2] == pytest.approx(a[2], rel=1e-12)
+
+
+def test_resident_solves_of_two_threads(gpu):
+    """Two handles on streams of their own, each driven by a thread: the
+    solves' blocks fill the chip, and each solve ends as it does alone."""
+    import threading
+    import torch
+    shapes = [(64, 64, 64), (64, 256, 256)]
+    want, got = [None, None], [[], []]
+    sims, rhs = [], []
+    for q, shape in enumerate(shapes):
+        nz, ny, nx = shape
+        with torch.cuda.stream(torch.cuda.Stream()):
+            p = li.workload("C1", nx=nx, ny=ny, nz=nz, precision="fp32",
+                            poisson_scheme="chebyshev", poisson_tol=1e-4)
+            sims.append(gpu.LES(p))
+        rhs.append(torch.from_numpy(li.random_field(shape, seed=50 + q)))
+        torch.cuda.synchronize()
+        phi, st, rc = sims[q].poisson_solve(rhs[q], fixed_sweeps=100)
+        want[q] = phi.cpu().numpy()
+
+    def run(q):
+        with torch.cuda.stream(sims[q].stream):
+            for _ in range(8):
+                phi, st, rc = sims[q].poisson_solve(rhs[q], fixed_sweeps=100)
+                got[q].append(phi.cpu().numpy())
+
+    threads = [threading.Thread(target=run, args=(q,)) for q in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for q in range(2):
+        assert len(got[q]) == 8
+        assert all(np.array_equal(a, want[q]) for a in got[q])
