@@ -34,26 +34,8 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 CASE_LABEL = {"cloud_layer": "synthetic stratocumulus",
               "bubble": "dry bubble (density current / rising bubble)"}
 
-# HBM bytes per launch of the one-sweep Chebyshev kernel measured with
-# rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (FETCH scaled x2.0, WRITE x1.0 by a
-# 1 GiB copy calibration); see profiles/sweep_kernel_hbm_traffic_pmc.md.
-# Valid only for the sweep source it was taken on (sha256 prefix).
-SWEEP_SOURCE = os.path.join(ROOT, "paper_2301_04698_amd", "csrc", "k_tsweep.hip")
+FP64_PEAK_TFLOPS = 78.6  # MI355X FP64 vector, published
 GUESS_WEIGHTS = os.path.join(ROOT, "paper_2301_04698_amd", "weights", "guess_256x256x128.npy")
-MEASURED_TRAFFIC = {
-    "sha256": "013a1b1cb19709d2",
-    "bytes": {(256, 256, 128): 104_610_944 + 33_554_432, (512, 512, 256): 841_642_816 + 268_435_456},
-}
-
-def measured_traffic(p, S):
-    import hashlib
-    if S != 1:
-        return None
-    with open(SWEEP_SOURCE, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()[:16]
-    if sha != MEASURED_TRAFFIC["sha256"]:
-        return None
-    return MEASURED_TRAFFIC["bytes"].get((p["nx"], p["ny"], p["nz"]))
 
 
 def parse():
@@ -116,7 +98,7 @@ def run_sweeps(args):
         "mode": "sweeps", "workload": args.workload, "grid": [p["nx"], p["ny"], p["nz"]],
         "precision": p["precision"], "scheme": p["poisson_scheme"], "sweeps": args.sweeps,
         "us_per_sweep": per * 1e6, "bytes_per_sweep": bpc * n,
-        "algorithmic_GBs": bpc * n / per / 1e9, "frac_of_8TBs": bpc * n / per / 1e9 / HBM_PEAK_GBS,
+        "form": sweep_form(p)[0], "algorithmic_GBs": bpc * n / per / 1e9, "frac_of_8TBs": bpc * n / per / 1e9 / HBM_PEAK_GBS,
         "note": "solve time includes rhs centring and the final residual check"}), flush=True)
 
 
@@ -139,21 +121,67 @@ def run_copy(args):
                       "us_per_copy": s * 1e6, "GBs_read_plus_write": 8 * n / s / 1e9}), flush=True)
 
 
-def sweep_kernel_name(p, S):
-    """Template instance of the plain (no residual check) sweep launch."""
-    es = 8 if p["precision"] == "fp64" else 4
-    cheb = "true" if p["poisson_scheme"] == "chebyshev" else "false"
-    T = "double" if es == 8 else "float"
-    if S != 1:
-        return f"sweep2_kernel<{T}, 4, {cheb}, false>"
-    streamed = 4.0 * p["nx"] * p["ny"] * p["nz"] * es > 192e6
-    if p["nx"] >= 256 and p["ny"] >= 4:
-        wx, ty = 4, (4 if streamed else 2)
+def _ceil(a, b):
+    return -(-a // b)
+
+
+def sweep_form(p):
+    """How the library runs the sweeps of a solve on p's grid: ("resident",
+    all of them), ("several", 2 or 3 per launch) or ("single", 1).  The rules
+    are those of k_psweep.hip and k_msweep.hip."""
+    nx, ny, nz = p["nx"], p["ny"], p["nz"]
+    f32, cheb = p["precision"] == "fp32", p["poisson_scheme"] == "chebyshev"
+    by = 64 if f32 else 32  # rows of a tile of several sweeps
+    asked = p.get("sweeps_per_launch", 0)
+    if asked:
+        return ("single", 1) if asked == 1 else ("several", asked)
+    if ny == 1:
+        boxes = [(1, 32), (1, 256)]
     else:
-        wx, ty = 1, (16 if streamed else 4)
-        if p["ny"] < ty:
-            ty = 1 if p["ny"] < 4 else 4
-    return f"sweep1_kernel<{T}, {wx}, {ty}, {cheb}, false, {'true' if streamed else 'false'}>"
+        boxes = [(8, 4), (8, 8), (16, 8) if f32 else (8, 16)]
+        if cheb:
+            boxes += [(16, 16)] + ([(16, 32)] if f32 else [])
+    if any(_ceil(nx, 64) * _ceil(ny, r) * _ceil(nz, z) <= 256 for r, z in boxes):
+        return "resident", None
+    cols = _ceil(nx, 58) * _ceil(ny, by - 6)
+    cost = min(_ceil(cols * n, 256) * (_ceil(nz, n) + 6) for n in range(1, min(nz, 64) + 1))
+    return ("several", 3) if cost * 256 * 64 * by <= 5 * nx * ny * nz else ("single", 1)
+
+
+def sweep_roofline(p, avg_sweep):
+    """What the plain sweeps reach against what bounds them, from the average
+    seconds of one of them."""
+    form, S = sweep_form(p)
+    ncell = p["nx"] * p["ny"] * p["nz"]
+    es = 8 if p["precision"] == "fp64" else 4
+    cheb = p["poisson_scheme"] == "chebyshev"
+    T = "double" if es == 8 else "float"
+    if form == "resident":
+        # the iterates never leave the chip: 3 + 1 + 6 + 1 + 2 (Chebyshev: + 3)
+        # FP64 operations per cell, an FMA as two, and two of the residual's sum
+        flops = (18 if cheb else 15) * ncell
+        tf = flops / avg_sweep / 1e12
+        return {
+            "bound": "fp64", "kernel": f"psweep_kernel<{T}>", "achieved": tf,
+            "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / FP64_PEAK_TFLOPS,
+            "avg_sweep_us": avg_sweep * 1e6, "sweeps_per_launch": "all of a solve",
+            "flops_per_sweep": flops,
+            "note": ("iterates in registers, right-hand side in LDS for the whole solve; one sweep "
+                     f"per launch would move {sweep_bytes_per_cell(p) * ncell / 1e6:.0f} MB"),
+        }
+    # one sweep: sweep_bytes_per_cell; several: 3 arrays in, 2 out
+    bytes_launch = (sweep_bytes_per_cell(p) if S == 1 else 5 * es) * ncell
+    achieved = bytes_launch / (avg_sweep * S) / 1e9
+    name = f"sweep1_kernel<{T}>" if S == 1 else f"msweep_kernel<{T}, {S}>"
+    return {
+        "bound": "hbm", "kernel": name, "achieved": achieved, "peak": HBM_PEAK_GBS,
+        "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "avg_sweep_us": avg_sweep * 1e6,
+        "sweeps_per_launch": S, "avg_launch_us": avg_sweep * S * 1e6,
+        "bytes_per_launch": bytes_launch,
+        "note": (f"bytes a launch cannot do without, {bytes_launch / 1e6:.0f} MB, "
+                 + ("inside" if bytes_launch < 256e6 else "beyond")
+                 + " the 256 MB Infinity Cache"),
+    }
 
 
 def sweep_bytes_per_cell(p):
@@ -383,10 +411,7 @@ def largest_domain(args):
     sim.close()
     del sim
     torch.cuda.empty_cache()
-    S = 1
     avg = st["sweep_seconds"] / max(st["sweeps_timed"], 1)
-    bytes_launch = sweep_bytes_per_cell(p) * ncell
-    achieved = bytes_launch / avg / 1e9
     learned["guess_passes"] = args.guess_passes
     learned["speedup"] = learned["value"] / plain["value"]
     learned["poisson_speedup"] = plain["poisson_s_per_step"] / learned["poisson_s_per_step"]
@@ -403,18 +428,7 @@ def largest_domain(args):
                  f"state; setup {t_init:.0f} s"),
         "plain": plain,
         "learned": learned,
-        "sweep": {
-            "bound": "hbm",
-            "kernel": sweep_kernel_name(p, S),
-            "achieved": achieved,
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
-            "avg_launch_us": avg * 1e6,
-            "bytes_per_launch": bytes_launch,
-            "note": ("plain sweeps between residual checks, HIP events on the library's stream; "
-                     "arrays of 4.3 GB per sweep, beyond the 256 MB Infinity Cache"),
-        },
+        "sweep": sweep_roofline(p, avg),
     }
 
 
@@ -473,13 +487,7 @@ def main():
     ms_step = wall / args.steps * 1e3
     value = ncell * args.steps / wall / 1e6
 
-    S = sim.cfg.sweeps_per_launch or 1
     avg_sweep = st["sweep_seconds"] / max(st["sweeps_timed"], 1)
-    avg_launch = avg_sweep * S
-    es = 4 if p["precision"] == "fp32" else 8
-    # one sweep: sweep_bytes_per_cell; two fused sweeps: 3 arrays in, 2 out
-    bytes_launch = (sweep_bytes_per_cell(p) if S == 1 else 5 * es) * ncell
-    achieved = bytes_launch / avg_launch / 1e9
     diag = sim.diagnostics()
 
     out = {
@@ -511,21 +519,7 @@ def main():
         "not_converged": st["not_converged"],
         "res_rel_max": st["res_rel_max"],
         "cfl": diag["cfl"],
-        "roofline": {
-            "bound": "hbm",
-            "kernel": sweep_kernel_name(p, S),
-            "achieved": achieved,
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS,
-            "traffic": measured_traffic(p, sim.cfg.sweeps_per_launch or 1),
-            "avg_launch_us": avg_launch * 1e6,
-            "sweeps_per_launch": S,
-            "bytes_per_launch": bytes_launch,
-            "note": (f"working set of the sweep {bytes_launch / 1e6:.0f} MB, "
-                     + ("inside" if bytes_launch < 256e6 else "beyond")
-                     + " the 256 MB Infinity Cache"),
-        },
+        "roofline": sweep_roofline(p, avg_sweep),
     }
     progress(f"{p['nx']}x{p['ny']}x{p['nz']}: plain form {value:.1f} Mcell-steps/s")
     if p["init"] != "cloud_layer":
