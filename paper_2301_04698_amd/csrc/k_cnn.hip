@@ -72,23 +72,6 @@ __device__ __forceinline__ Cell decode(int64_t q, int nz, int ny, int nx) {
   return c;
 }
 
-// Input cell read by output cell c at tap (dz, dy, dx): even mirror in z
-// (radius one: -1 -> 0, nz -> nz - 1), wrap or valid offset in x and y.
-__device__ __forceinline__ int64_t src_cell(const CnnGeom &G, const Cell &c, int dz, int dy,
-                                            int dx) {
-  int kk = c.k + dz;
-  kk = kk < 0 ? 0 : (kk >= G.nz ? G.nz - 1 : kk);
-  int jj, ii;
-  if (G.periodic) {
-    jj = pwrap(c.j + dy, G.nyi);
-    ii = pwrap(c.i + dx, G.nxi);
-  } else {
-    jj = c.j + 1 + dy;
-    ii = c.i + 1 + dx;
-  }
-  return (((int64_t)c.b * G.nz + kk) * G.nyi + jj) * G.nxi + ii;
-}
-
 // ------------------------------------------------------------- forward
 
 __global__ __launch_bounds__(kBlock) void pack_kernel(const float *__restrict__ params,
