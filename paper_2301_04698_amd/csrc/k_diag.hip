@@ -21,8 +21,8 @@ constexpr int kDiagParts = 13;  // values of a part of a level
 // blockIdx.x: part of level blockIdx.y's rows.  A wave takes a row at a time,
 // so that a cell's indices need no division; the sums run over a fixed order
 // and are deterministic.  Bound by memory, 7 fields read once: 256 x 256 x 128
-// FP32 74 us; with one block per level (128 of 256 CUs, a 64-bit division per
-// cell) it took 289 us.
+// FP32 63 us (74 with two barriers per value summed); with one block per level
+// (128 of 256 CUs, a 64-bit division per cell) it took 289 us.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, Profiles<T> P,
                                                       const T *__restrict__ u,
@@ -73,17 +73,24 @@ __global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, Profiles<T> P,
       a.cmax = fmax(a.cmax, fabs(uu) * cx + fabs(vv) * cy + fabs(ww) * cz);
     }
   }
-  double *out = parts + ((int64_t)k * gridDim.x + blockIdx.x) * kDiagParts;
+  // the waves' values, in order; one barrier for all of them
+  __shared__ double red[NW][kDiagParts];
 #pragma unroll
   for (int m = 0; m < 11; ++m) {
-    const double s = block_sum(a.s[m]);
-    if (threadIdx.x == 0) out[m] = s;
+    const double s = wave_sum(a.s[m]);
+    if (lane == 0) red[wave][m] = s;
   }
-  const double dm = block_max(a.dmax), cm = block_max(a.cmax);
-  if (threadIdx.x == 0) {
-    out[11] = dm;
-    out[12] = cm;
+  const double dm = wave_max(a.dmax), cm = wave_max(a.cmax);
+  if (lane == 0) {
+    red[wave][11] = dm;
+    red[wave][12] = cm;
   }
+  __syncthreads();
+  const int m = threadIdx.x;
+  if (m >= kDiagParts) return;
+  double s = red[0][m];
+  for (int q = 1; q < NW; ++q) s = m < 11 ? s + red[q][m] : fmax(s, red[q][m]);
+  parts[((int64_t)k * gridDim.x + blockIdx.x) * kDiagParts + m] = s;
 }
 
 // The parts of a level, in order, into its row of the output: thread m of
@@ -111,11 +118,11 @@ __global__ __launch_bounds__(64) void diag_final_kernel(Profiles<T> P, int npart
 
 }  // namespace
 
-// Parts of a level: blocks for several on each CU, rows for each of a block's
-// waves.
+// Parts of a level: four blocks on each CU (eight: 4 us more at 256 x 256 x
+// 128), rows for each of a block's waves.
 static int diag_parts(const Grid &g) {
   const int rows = (g.ny + kBlock / 64 - 1) / (kBlock / 64);
-  return std::max(1, std::min(rows, (2047 + g.nz) / g.nz));
+  return std::max(1, std::min(rows, (1023 + g.nz) / g.nz));
 }
 
 size_t diag_part_values(const Grid &g) { return (size_t)g.nz * diag_parts(g) * kDiagParts; }
