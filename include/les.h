@@ -268,6 +268,24 @@ typedef struct les_diag {
   double ke;         /* sum rho0 |u|^2 / 2 dV (J) */
 } les_diag;
 
+/* How the sweeps of a handle's solves run, and how they have run so far. */
+typedef struct les_solver_info {
+  int32_t resident_blocks;   /* > 0: a solve (of a cap of at most 2^20 sweeps)
+                                is one launch of so many blocks, its iterates
+                                resident on the chip; 0: launch by launch */
+  int32_t sweeps_per_launch; /* launch by launch: at most so many in one */
+  int64_t resident_passes;   /* passes of sweeps that ran resident to their
+                                end (a solve repeated or continued has more
+                                than one) */
+  int64_t launches[3];       /* sweep launches made launch by launch: of one,
+                                two and three sweeps */
+  int32_t gave_up;           /* resident passes that waited too long (two
+                                seconds) for another block: repeated launch by
+                                launch, as all later solves of the handle */
+  int32_t refused;           /* resident launches that the runtime refused:
+                                as above */
+} les_solver_info;
+
 #define LES_NPROFILES 9  /* thl, qt, ql, u, v, w, w^2, w^3, b (horizontal means) */
 
 /* Fills Table 1 of the paper and defaults for the rest (a 32^3 grid). */
@@ -305,6 +323,12 @@ int les_step(les_handle *h, int32_t nsteps, const les_step_opts *opts, les_step_
  * Synchronizes the stream. */
 int les_poisson_solve(les_handle *h, const void *rhs, void *phi, const les_poisson_opts *opts,
                       les_solve_stats *stats);
+
+/* How the solves of a configuration would run on this GPU type (host only,
+ * needs no GPU; the counts are zero), and how those of a handle run and have
+ * run. */
+int les_solver_plan(const les_config *cfg, les_solver_info *out);
+int les_solver_state(const les_handle *h, les_solver_info *out);
 
 /* The whole pressure perturbation p' (Sec. 2.4: the sum of the pressure
  * corrections rho0 phi of the solves): p_out (device, n elements of the

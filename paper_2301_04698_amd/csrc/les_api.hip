@@ -244,6 +244,7 @@ struct les_handle {
   bool resident;                 // solves run resident on the chip where their cap allows
   uint32_t tag;                  // first unused tag of the resident solves' exchange words
   int64_t steps_done;            // time steps taken since les_init (or the imported count)
+  les_solver_info ran;           // how the solves have run (its counts)
 };
 
 namespace {
@@ -440,13 +441,23 @@ SweepWeights sweep_weights(const les_handle *h) {
                       (h->mu_max - h->mu_min) / (h->mu_max + h->mu_min)};
 }
 
+// How the solves of a configuration run where the GPU takes resident launches.
+les_solver_info plan_of(const les_config *c) {
+  const Grid g = grid_of(c);
+  const bool cheb = c->poisson_scheme == LES_CHEBYSHEV, fp64 = c->precision == LES_FP64;
+  les_solver_info p;
+  std::memset(&p, 0, sizeof(p));
+  if (c->sweeps_per_launch == 0)
+    p.resident_blocks = fp64 ? psweep_blocks<double>(g, cheb) : psweep_blocks<float>(g, cheb);
+  p.sweeps_per_launch = fp64 ? msweep_depth<double>(g, c->sweeps_per_launch)
+                             : msweep_depth<float>(g, c->sweeps_per_launch);
+  return p;
+}
+
 // A resident solve's blocks wait for each other, so all of them have to be
 // on the GPU at once: a cooperative launch of at most one block per CU.
 bool resident_fits(const les_handle *h) {
-  if (h->lay.n_words == 0) return false;
-  const bool cheb = h->cfg.poisson_scheme == LES_CHEBYSHEV;
-  const int nb = h->cfg.precision == LES_FP64 ? psweep_blocks<double>(h->grid, cheb)
-                                              : psweep_blocks<float>(h->grid, cheb);
+  const int nb = plan_of(&h->cfg).resident_blocks;
   int dev = 0, coop = 0, cus = 0;
   const bool ok =
       hipGetDevice(&dev) == hipSuccess &&
@@ -544,6 +555,7 @@ bool launch_resident(les_handle *h, View<T> &V, const T *rhs, const T *rhs_kept,
                        s) != hipSuccess) {
     (void)hipGetLastError();
     h->resident = false;
+    ++h->ran.refused;
     return false;
   }
   return true;
@@ -693,6 +705,7 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
     // checking launch can decide the check before it.
     const bool decides = pend_m >= 0 && L.S == 1;
     double *parts = (nchecks & 1) ? V.partials2 : V.partials;
+    ++h->ran.launches[L.S - 1];
     // The first Chebyshev sweep has weight 1: the plain weighted-Jacobi
     // sweep, which must not read the (uninitialised) previous iterate.
     if (L.S == 1)
@@ -856,6 +869,7 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
           if (r.done == 0 || r.stop_m < 0)
             return fail(LES_ERR_STATE, "Poisson solve ended without a decision");
           h->tag += (uint32_t)r.stop_m + 2;
+          ++h->ran.resident_passes;
           if (timed && r.stop_m > 0) {
             float ms = 0.f;
             HIP_TRY(hipEventElapsedTime(&ms, h->ev_sweep[0], h->ev_sweep[1]));
@@ -867,6 +881,7 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
           return LES_OK;
         }
         h->resident = V.res = false;
+        ++h->ran.gave_up;
         launch_ctl_rerun(V.ctl, s);
         launch_zero<T>(g, V.f[F_PHI0], s);
       }
@@ -1455,9 +1470,8 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->steps_done = 0;
   h->resident = resident_fits(h);
   h->tag = 1;
-  h->sweeps_per_launch = cfg->precision == LES_FP64
-                             ? msweep_depth<double>(h->grid, cfg->sweeps_per_launch)
-                             : msweep_depth<float>(h->grid, cfg->sweeps_per_launch);
+  h->sweeps_per_launch = plan_of(cfg).sweeps_per_launch;
+  std::memset(&h->ran, 0, sizeof(h->ran));
 
   auto cleanup = [&](int code) {
     les_destroy(h);
@@ -1623,6 +1637,23 @@ int les_import_state(les_handle *h, const void *src) {
   for (int k = 0; k < c.n_subiter; ++k) h->hist_valid[k] = (hd.hist_valid >> k) & 1;
   h->zero_sweeps = zsw;
   h->steps_done = hd.steps_done;
+  return LES_OK;
+}
+
+int les_solver_plan(const les_config *cfg, les_solver_info *out) {
+  int rc = validate(cfg);
+  if (rc) return rc;
+  if (!out) return fail(LES_ERR_ARG, "out is NULL");
+  *out = plan_of(cfg);
+  return LES_OK;
+}
+
+int les_solver_state(const les_handle *h, les_solver_info *out) {
+  if (!h || !out) return fail(LES_ERR_ARG, "handle and out must be non-NULL");
+  const les_solver_info p = plan_of(&h->cfg);
+  *out = h->ran;
+  out->resident_blocks = h->resident ? p.resident_blocks : 0;
+  out->sweeps_per_launch = h->sweeps_per_launch;
   return LES_OK;
 }
 

@@ -41,9 +41,10 @@ WS_FIELDS = ("un", "vn", "wn", "thl_half", "qt_half", "thl_mid", "qt_mid", "uh",
              "phi2", "phi3", "p_prev", "guess", "rhs_defect")
 
 EXPORTS = ("les_default_config", "les_workspace_bytes", "les_workspace_offset", "les_init",
-           "les_step", "les_poisson_solve", "les_pressure", "les_set_pressure_profile",
-           "les_thermo", "les_diagnostics", "les_state_bytes", "les_export_state",
-           "les_import_state", "les_steps_done", "les_destroy", "les_last_error")
+           "les_step", "les_poisson_solve", "les_solver_plan", "les_solver_state",
+           "les_pressure", "les_set_pressure_profile", "les_thermo", "les_diagnostics",
+           "les_state_bytes", "les_export_state", "les_import_state", "les_steps_done",
+           "les_destroy", "les_last_error")
 
 
 class LesConfig(C.Structure):
@@ -106,6 +107,16 @@ class LesStepStats(C.Structure):
         return {n: getattr(self, n) for n, _ in self._fields_}
 
 
+class LesSolverInfo(C.Structure):
+    _fields_ = [("resident_blocks", C.c_int32), ("sweeps_per_launch", C.c_int32),
+                ("resident_passes", C.c_int64), ("launches", C.c_int64 * 3),
+                ("gave_up", C.c_int32), ("refused", C.c_int32)]
+
+    def as_dict(self):
+        return {n: list(v) if n == "launches" else v
+                for n, v in ((n, getattr(self, n)) for n, _ in self._fields_)}
+
+
 class LesDiag(C.Structure):
     _fields_ = [(n, C.c_double) for n in ("mass_thl", "mass_qt", "div_l2", "div_max", "cfl", "ke")]
 
@@ -138,6 +149,8 @@ def load():
     L.les_step.argtypes = [C.c_void_p, C.c_int32, C.POINTER(LesStepOpts), C.POINTER(LesStepStats)]
     L.les_poisson_solve.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(LesPoissonOpts),
                                     C.POINTER(LesSolveStats)]
+    L.les_solver_plan.argtypes = [cp, C.POINTER(LesSolverInfo)]
+    L.les_solver_state.argtypes = [C.c_void_p, C.POINTER(LesSolverInfo)]
     L.les_pressure.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_double)]
     L.les_set_pressure_profile.argtypes = [C.c_void_p, C.POINTER(C.c_double)]
     L.les_state_bytes.argtypes = [C.c_void_p]
@@ -216,6 +229,13 @@ def workspace_offset(cfg: LesConfig, field) -> int:
     off = C.c_size_t()
     check(load().les_workspace_offset(C.byref(cfg), fid, C.byref(off)))
     return int(off.value)
+
+
+def solver_plan(cfg: LesConfig) -> dict:
+    """How the solves of a configuration would run (les_solver_plan)."""
+    info = LesSolverInfo()
+    check(load().les_solver_plan(C.byref(cfg), C.byref(info)), allow_warn=False)
+    return info.as_dict()
 
 
 class LES:
@@ -336,6 +356,12 @@ class LES:
         rc = check(load().les_poisson_solve(self.handle, C.c_void_p(rhs.data_ptr()),
                                             C.c_void_p(phi.data_ptr()), C.byref(opts), C.byref(st)))
         return phi, st.as_dict(), rc
+
+    def solver_state(self):
+        """How this handle's solves run and have run (les_solver_state)."""
+        info = LesSolverInfo()
+        check(load().les_solver_state(self.handle, C.byref(info)), allow_warn=False)
+        return info.as_dict()
 
     def thermo(self, thl, qt):
         torch = self.torch

@@ -204,3 +204,28 @@ def test_learned_guess_workspace(lib):
     # three input channels and the larger parameter vector
     learned3 = lib.workspace_bytes(lib.make_config(dict(p, guess="learned3")))
     assert learned3 >= base + n * 8 + n * (4 + 6 + 2 * 32) + 15601 * 6
+
+
+def test_solver_info_layout_and_plan(lib, tmp_path):
+    prog = tmp_path / "si.c"
+    prog.write_text(r'''
+#include "les.h"
+#include <stdio.h>
+#include <stddef.h>
+int main(void) {
+  printf("%zu %zu %zu\n", sizeof(les_solver_info), offsetof(les_solver_info, launches),
+         offsetof(les_solver_info, refused));
+  return 0;
+}''')
+    exe = tmp_path / "si"
+    subprocess.run(["gcc", "-I", os.path.join(ROOT, "include"), str(prog), "-o", str(exe)], check=True)
+    got = [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True).stdout.split()]
+    I = lib.LesSolverInfo
+    assert got == [C.sizeof(I), I.launches.offset, I.refused.offset]
+    plan = lib.solver_plan(lib.make_config(li.workload("C1", nx=64, ny=64, nz=64, precision="fp32")))
+    assert plan["resident_blocks"] == 128 and plan["launches"] == [0, 0, 0]
+    plan = lib.solver_plan(lib.make_config(li.workload("C1", sweeps_per_launch=1)))
+    assert plan["resident_blocks"] == 0 and plan["sweeps_per_launch"] == 1
+    with pytest.raises(lib.LesError):
+        lib.solver_plan(lib.make_config(li.workload("C1", dt=0.0)))
+    assert lib.load().les_solver_state(None, C.byref(I())) == lib.LES_ERR_ARG

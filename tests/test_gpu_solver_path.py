@@ -1,0 +1,92 @@
+"""Which way a solve ran, as the library reports it: the comparisons of the
+resident and of the several-sweep kernels with the one-sweep launches hold
+only where those kernels ran."""
+import threading
+
+import numpy as np
+import pytest
+
+import les_inputs as li
+from test_gpu_multisweep import CASES as SEVERAL
+from test_gpu_resident import CASES as RESIDENT
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2301_04698_amd import les
+    les.load()
+    return les
+
+
+def workload(precision, scheme, shape, **kw):
+    nz, ny, nx = shape
+    return li.workload("C1", nx=nx, ny=ny, nz=nz, precision=precision, poisson_scheme=scheme,
+                       poisson_tol=1e-4, poisson_max_sweeps=600, poisson_check_every=7, **kw)
+
+
+@pytest.mark.parametrize("precision,scheme,shape", RESIDENT)
+def test_resident_cases_run_resident(gpu, precision, scheme, shape):
+    import torch
+    print(f"resident {precision} {scheme} {shape}", flush=True)
+    sim = gpu.LES(workload(precision, scheme, shape))
+    plan = gpu.solver_plan(sim.cfg)
+    assert plan["resident_blocks"] > 0
+    rhs = torch.from_numpy(li.random_field(shape, seed=17))
+    for fixed in (1, 38, 0):
+        sim.poisson_solve(rhs, fixed_sweeps=fixed)
+    got = sim.solver_state()
+    assert got == dict(plan, resident_passes=3)
+
+
+# the FP32 Jacobi entry of the shared list runs one sweep per launch; a grid
+# well inside the rule for three takes its place here
+ONE_BY_ONE = ("fp32", "jacobi", (64, 100, 300))
+
+
+@pytest.mark.parametrize("precision,scheme,shape",
+                         [c for c in SEVERAL if c != ONE_BY_ONE]
+                         + [("fp32", "jacobi", (135, 180, 530))])
+def test_several_sweeps_run_in_a_launch(gpu, precision, scheme, shape):
+    import torch
+    print(f"several sweeps per launch {precision} {scheme} {shape}", flush=True)
+    rhs = torch.from_numpy(li.random_field(shape, seed=19))
+    want = None
+    for S, depth in ((1, 1), (2, 2), (0, 3)):
+        sim = gpu.LES(workload(precision, scheme, shape, sweeps_per_launch=S))
+        out = [sim.poisson_solve(rhs, fixed_sweeps=f)[0].cpu().numpy() for f in (1, 2, 3, 5, 22)]
+        got = sim.solver_state()
+        sim.close()
+        assert got["resident_blocks"] == 0 and got["sweeps_per_launch"] == depth
+        assert [n > 0 for n in got["launches"]][depth - 1:] == [True] + [False] * (3 - depth)
+        want = want or out
+        assert all(np.array_equal(a, b) for a, b in zip(want, out))
+
+
+def test_resident_solves_of_two_threads_give_up_no_wait(gpu):
+    import torch
+    shapes = [(64, 64, 64), (64, 256, 256)]
+    sims, rhs = [], []
+    for q, shape in enumerate(shapes):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            sims.append(gpu.LES(workload("fp32", "chebyshev", shape)))
+        rhs.append(torch.from_numpy(li.random_field(shape, seed=50 + q)))
+
+    def run(q):
+        with torch.cuda.stream(sims[q].stream):
+            for _ in range(8):
+                sims[q].poisson_solve(rhs[q], fixed_sweeps=100)
+
+    threads = [threading.Thread(target=run, args=(q,)) for q in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for sim in sims:
+        got = sim.solver_state()
+        assert (got["resident_passes"], got["gave_up"], got["refused"]) == (8, 0, 0)
+        assert got["launches"] == [0, 0, 0]
