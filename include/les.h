@@ -330,6 +330,15 @@ int les_poisson_solve(les_handle *h, const void *rhs, void *phi, const les_poiss
 int les_solver_plan(const les_config *cfg, les_solver_info *out);
 int les_solver_state(const les_handle *h, les_solver_info *out);
 
+/* For tests of what follows when a resident pass cannot be used: of the
+ * handle's coming resident passes the one after `after` others is refused at
+ * its launch (LES_FAULT_REFUSED) or gives up the first wait that has not ended
+ * when it looks (LES_FAULT_WAIT); once.  next_tag: the number that the next
+ * pass's first iterate takes in the exchange between blocks, not below one
+ * already used (0: leave it). */
+enum { LES_FAULT_NONE = 0, LES_FAULT_REFUSED = 1, LES_FAULT_WAIT = 2 };
+int les_resident_fault(les_handle *h, int32_t fault, int32_t after, uint32_t next_tag);
+
 /* The whole pressure perturbation p' (Sec. 2.4: the sum of the pressure
  * corrections rho0 phi of the solves): p_out (device, n elements of the
  * storage type, nullable) = p + pbar(z), rounded once; pbar_host (host, nz

@@ -13,6 +13,7 @@
 #include <cstring>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "api_util.h"
@@ -245,6 +246,7 @@ struct les_handle {
   uint32_t tag;                  // first unused tag of the resident solves' exchange words
   int64_t steps_done;            // time steps taken since les_init (or the imported count)
   les_solver_info ran;           // how the solves have run (its counts)
+  int32_t fault, fault_after;    // les_resident_fault: what, after so many resident passes
 };
 
 namespace {
@@ -550,9 +552,12 @@ bool launch_resident(les_handle *h, View<T> &V, const T *rhs, const T *rhs_kept,
     launch_clear_words(words, h->lay.n_words, s);
     h->tag = 1;
   }
-  if (launch_psweep<T>(h->grid, c.poisson_scheme == LES_CHEBYSHEV, w.omega_j, w.rho,
+  int32_t fault = LES_FAULT_NONE;
+  if (h->fault != LES_FAULT_NONE && h->fault_after-- <= 0) std::swap(fault, h->fault);
+  if (fault == LES_FAULT_REFUSED ||
+      launch_psweep<T>(h->grid, c.poisson_scheme == LES_CHEBYSHEV, w.omega_j, w.rho,
                        c.poisson_check_every, h->tag, rhs, rhs_kept, V.f[F_PHI0], words, V.ctl,
-                       s) != hipSuccess) {
+                       fault == LES_FAULT_WAIT, s) != hipSuccess) {
     (void)hipGetLastError();
     h->resident = false;
     ++h->ran.refused;
@@ -1472,6 +1477,8 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->tag = 1;
   h->sweeps_per_launch = plan_of(cfg).sweeps_per_launch;
   std::memset(&h->ran, 0, sizeof(h->ran));
+  h->fault = LES_FAULT_NONE;
+  h->fault_after = 0;
 
   auto cleanup = [&](int code) {
     les_destroy(h);
@@ -1654,6 +1661,20 @@ int les_solver_state(const les_handle *h, les_solver_info *out) {
   *out = h->ran;
   out->resident_blocks = h->resident ? p.resident_blocks : 0;
   out->sweeps_per_launch = h->sweeps_per_launch;
+  return LES_OK;
+}
+
+int les_resident_fault(les_handle *h, int32_t fault, int32_t after, uint32_t next_tag) {
+  int rc = check_handle(h);
+  if (rc) return rc;
+  if (fault < LES_FAULT_NONE || fault > LES_FAULT_WAIT || after < 0)
+    return fail(LES_ERR_ARG, "unknown fault %d after %d passes", fault, after);
+  // tags used before must not come again
+  if (next_tag != 0 && next_tag < h->tag)
+    return fail(LES_ERR_ARG, "next_tag is below the first unused tag %u", h->tag);
+  h->fault = fault;
+  h->fault_after = after;
+  if (next_tag != 0) h->tag = next_tag;
   return LES_OK;
 }
 

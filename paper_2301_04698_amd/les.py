@@ -29,6 +29,7 @@ LES_MEAN_SWEPT, LES_MEAN_LEVEL, LES_MEAN_EXACT = 0, 1, 2
 MEAN_MODES = {"swept": LES_MEAN_SWEPT, "level": LES_MEAN_LEVEL, "exact": LES_MEAN_EXACT}
 LES_GUESS_ZERO, LES_GUESS_EXTRAPOLATE, LES_GUESS_PREVIOUS, LES_GUESS_LEARNED = 0, 1, 2, 3
 LES_GUESS_LEARNED3 = 4
+LES_FAULT_NONE, LES_FAULT_REFUSED, LES_FAULT_WAIT = 0, 1, 2
 GUESS_MODES = {"zero": LES_GUESS_ZERO, "extrapolate": LES_GUESS_EXTRAPOLATE,
                "previous": LES_GUESS_PREVIOUS, "learned": LES_GUESS_LEARNED,
                "learned3": LES_GUESS_LEARNED3}
@@ -42,9 +43,9 @@ WS_FIELDS = ("un", "vn", "wn", "thl_half", "qt_half", "thl_mid", "qt_mid", "uh",
 
 EXPORTS = ("les_default_config", "les_workspace_bytes", "les_workspace_offset", "les_init",
            "les_step", "les_poisson_solve", "les_solver_plan", "les_solver_state",
-           "les_pressure", "les_set_pressure_profile", "les_thermo", "les_diagnostics",
-           "les_state_bytes", "les_export_state", "les_import_state", "les_steps_done",
-           "les_destroy", "les_last_error")
+           "les_resident_fault", "les_pressure", "les_set_pressure_profile", "les_thermo",
+           "les_diagnostics", "les_state_bytes", "les_export_state", "les_import_state",
+           "les_steps_done", "les_destroy", "les_last_error")
 
 
 class LesConfig(C.Structure):
@@ -151,6 +152,7 @@ def load():
                                     C.POINTER(LesSolveStats)]
     L.les_solver_plan.argtypes = [cp, C.POINTER(LesSolverInfo)]
     L.les_solver_state.argtypes = [C.c_void_p, C.POINTER(LesSolverInfo)]
+    L.les_resident_fault.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_uint32]
     L.les_pressure.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_double)]
     L.les_set_pressure_profile.argtypes = [C.c_void_p, C.POINTER(C.c_double)]
     L.les_state_bytes.argtypes = [C.c_void_p]
@@ -362,6 +364,11 @@ class LES:
         info = LesSolverInfo()
         check(load().les_solver_state(self.handle, C.byref(info)), allow_warn=False)
         return info.as_dict()
+
+    def resident_fault(self, fault=LES_FAULT_NONE, after=0, next_tag=0):
+        """For tests: a coming resident pass fails (les_resident_fault)."""
+        check(load().les_resident_fault(self.handle, int(fault), int(after), int(next_tag)),
+              allow_warn=False)
 
     def thermo(self, thl, qt):
         torch = self.torch
