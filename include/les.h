@@ -332,8 +332,8 @@ int les_solver_state(const les_handle *h, les_solver_info *out);
 
 /* For tests of what follows when a resident pass cannot be used: of the
  * handle's coming resident passes the one after `after` others is refused at
- * its launch (LES_FAULT_REFUSED) or gives up the first wait that has not ended
- * when it looks (LES_FAULT_WAIT); once.  next_tag: the number that the next
+ * its launch (LES_FAULT_REFUSED) or has a block that waits for no other, as
+ * after a wait it gave up (LES_FAULT_WAIT); once.  next_tag: the number that the next
  * pass's first iterate takes in the exchange between blocks, not below one
  * already used (0: leave it). */
 enum { LES_FAULT_NONE = 0, LES_FAULT_REFUSED = 1, LES_FAULT_WAIT = 2 };

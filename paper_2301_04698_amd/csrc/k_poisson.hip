@@ -759,6 +759,12 @@ void launch_ctl_budget(SolveCtl *ctl, int max_sweeps, hipStream_t s) {
   ctl_budget_kernel<<<1, 64, 0, s>>>(ctl, max_sweeps);
 }
 
+__global__ void ctl_abort_kernel(SolveCtl *ctl) {
+  if (threadIdx.x == 0) ctl->aborted = 1;
+}
+
+void launch_ctl_abort(SolveCtl *ctl, hipStream_t s) { ctl_abort_kernel<<<1, 64, 0, s>>>(ctl); }
+
 __global__ void ctl_rerun_kernel(SolveCtl *ctl) {
   if (threadIdx.x != 0) return;
   ctl->done = 0;

@@ -67,7 +67,7 @@ size_t psweep_words(const Grid &g, bool chebyshev) {
 template <typename T>
 hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double rho, int every,
                          uint32_t base, const T *rhs, const T *rhs_kept, T *out, uint64_t *words,
-                         SolveCtl *ctl, bool impatient, hipStream_t s) {
+                         SolveCtl *ctl, hipStream_t s) {
   const Fit f = fit_of<T>(g, chebyshev);
   PArgs<T> a;
   a.g = g;
@@ -85,7 +85,6 @@ hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double r
   a.faces = words;
   a.red = words + (size_t)f.nb * 2 * f.face;
   a.ctl = ctl;
-  a.wait_mask = impatient ? 0u : 63u;
   using S = Shapes<T>;
 #define LES_BOX(B)                                                            \
   (chebyshev ? (f.rag ? launch_box<typename S::B, true, true>(a, f.nb, s)     \
@@ -114,7 +113,7 @@ hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double r
   template size_t psweep_words<T>(const Grid &, bool);                                           \
   template hipError_t launch_psweep<T>(const Grid &, bool, double, double, int, uint32_t,        \
                                        const T *, const T *, T *, uint64_t *, SolveCtl *,        \
-                                       bool, hipStream_t);
+                                       hipStream_t);
 LES_INST(float)
 LES_INST(double)
 #undef LES_INST

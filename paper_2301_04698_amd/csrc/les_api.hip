@@ -554,10 +554,11 @@ bool launch_resident(les_handle *h, View<T> &V, const T *rhs, const T *rhs_kept,
   }
   int32_t fault = LES_FAULT_NONE;
   if (h->fault != LES_FAULT_NONE && h->fault_after-- <= 0) std::swap(fault, h->fault);
+  if (fault == LES_FAULT_WAIT) launch_ctl_abort(V.ctl, s);
   if (fault == LES_FAULT_REFUSED ||
       launch_psweep<T>(h->grid, c.poisson_scheme == LES_CHEBYSHEV, w.omega_j, w.rho,
                        c.poisson_check_every, h->tag, rhs, rhs_kept, V.f[F_PHI0], words, V.ctl,
-                       fault == LES_FAULT_WAIT, s) != hipSuccess) {
+                       s) != hipSuccess) {
     (void)hipGetLastError();
     h->resident = false;
     ++h->ran.refused;

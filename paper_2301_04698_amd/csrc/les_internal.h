@@ -217,9 +217,8 @@ void launch_msweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
 // stream ctl holds the outcome and out, which is zero before, phi.  With
 // rhs_kept (nullable) the right-hand side is that if ctl->guess_kept.  base:
 // iterates are tagged base .. base + sweeps + 1, none of them used on this
-// buffer since it was cleared.  ctl->aborted: a wait was given up, after two
-// seconds (impatient: if it has not ended when it first looks), and the result
-// is not valid.
+// buffer since it was cleared.  ctl->aborted: a wait was given up and the
+// result is not valid.
 constexpr int kResidentBlocks = 256;
 template <typename T>
 int psweep_blocks(const Grid &g, bool chebyshev);
@@ -228,9 +227,11 @@ size_t psweep_words(const Grid &g, bool chebyshev);
 template <typename T>
 hipError_t launch_psweep(const Grid &g, bool chebyshev, double omega_j, double rho, int every,
                          uint32_t base, const T *rhs, const T *rhs_kept, T *out, uint64_t *words,
-                         SolveCtl *ctl, bool impatient, hipStream_t s);
+                         SolveCtl *ctl, hipStream_t s);
 // w[0 .. n) = 0.
 void launch_clear_words(uint64_t *w, size_t n, hipStream_t s);
+// ctl->aborted = 1 (tests: the next resident launch's first block does not wait).
+void launch_ctl_abort(SolveCtl *ctl, hipStream_t s);
 // The sweeps start over after an aborted resident solve: ctl as before it.
 void launch_ctl_rerun(SolveCtl *ctl, hipStream_t s);
 

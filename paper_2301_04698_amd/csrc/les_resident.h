@@ -42,7 +42,7 @@
 // sum (two tagged words) and every block sums all of them in one order, so
 // all take the same decision.  The launch is cooperative: its blocks are
 // resident together, so every wait ends.  Each wait is bounded all the same
-// (kWaitTicks); a block that gives up sets ctl->aborted and every block runs
+// (kSpinTicks); a block that gives up sets ctl->aborted and every block runs
 // to its end without waiting, and the host repeats the solve launch by launch.
 #pragma once
 
@@ -57,7 +57,7 @@ namespace resident {
 
 constexpr int kNW = 8, kNT = 64 * kNW;
 // Ticks of the constant 100 MHz clock a wait may take: 2 s.
-constexpr uint64_t kWaitTicks = 200000000ull;
+constexpr uint64_t kSpinTicks = 200000000ull;
 
 // Box shapes.  D2: one row (ny = 1), waves stacked in z.  GL: levels per
 // group.  RV: right-hand side vectors (GL levels of a row) kept in
@@ -103,7 +103,6 @@ struct PArgs {
   uint64_t *faces;  // two parities of FACE words per block
   uint64_t *red;    // two slots of (block partial as two words)
   SolveCtl *ctl;
-  uint32_t wait_mask;  // a wait looks at the clock every (wait_mask + 1)-th round
 };
 
 // A word's place: a pointer uniform over the wave and a byte offset per lane
@@ -129,15 +128,13 @@ __device__ __forceinline__ bool has_tag(uint64_t w, uint32_t tag) {
   return (uint32_t)(w >> 32) == tag;
 }
 
-// One more round of a wait that began at t0 (every (mask + 1)-th looks at the
-// clock): false once it has lasted too long (mask 0: at once) or another wait
-// has.
-__device__ __forceinline__ bool keep_waiting(uint32_t n, uint64_t &t0, SolveCtl *ctl,
-                                             uint32_t mask) {
-  if ((n & mask) != 0) return true;
+// One more round of a wait that began at t0 (every 64th looks at the clock):
+// false once it has lasted too long or another wait has.
+__device__ __forceinline__ bool keep_waiting(uint32_t n, uint64_t &t0, SolveCtl *ctl) {
+  if ((n & 63u) != 0) return true;
   const uint64_t t = wall_clock64();
-  if (n == mask + 1u) t0 = t;
-  const bool late = mask == 0 || t - t0 > kWaitTicks;
+  if (n == 64u) t0 = t;
+  const bool late = t - t0 > kSpinTicks;
   if (late) __hip_atomic_store(&ctl->aborted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return !late && !__hip_atomic_load(&ctl->aborted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -315,7 +312,8 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
     if (threadIdx.x == 0) sh.dead = 0;
   }
   T zl[R], zh[R];  // the level below / above this thread's, per row
-  bool dead = false;
+  // (set before the launch, by tests only, it makes block 0 one that gave up)
+  bool dead = blockIdx.x == 0 && ctl->aborted != 0;
   __syncthreads();
 
   // the lane, forgotten at every group: addresses are made from it where they
@@ -411,7 +409,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
 #pragma unroll
         for (int q = 0; q < R * NWD; ++q) ok &= has_tag(wh[q], t);
       if (__all(ok)) break;
-      if (!keep_waiting(n, t0, ctl, a.wait_mask)) dead = true;
+      if (!keep_waiting(n, t0, ctl)) dead = true;
       issue(gn, t);
     }
     if constexpr (!B::D2)
@@ -755,7 +753,7 @@ __global__ __launch_bounds__(kNT) void psweep_kernel(PArgs<typename B::T> a) {
       const Word p0{red, (uint32_t)min((int)threadIdx.x, nb - 1) * 16u}, p1{red + 1, p0.off};
       uint64_t w0 = get_word(p0), w1 = get_word(p1), t0 = 0;
       for (uint32_t n = 1; !dead && !__all(has_tag(w0, t) && has_tag(w1, t)); ++n) {
-        if (!keep_waiting(n, t0, ctl, a.wait_mask)) dead = true;
+        if (!keep_waiting(n, t0, ctl)) dead = true;
         w0 = get_word(p0);
         w1 = get_word(p1);
       }

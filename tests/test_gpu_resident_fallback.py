@@ -1,5 +1,5 @@
 """Resident passes that cannot be used: one whose launch is refused, one that
-gives up a wait (its limit is set to nothing from the host; every block still
+gives up a wait (a block is told from the host not to wait; every block still
 runs to its end).  The solve is repeated launch by launch and ends as one that
 ran so from the start, bit for bit; and tags that are used up start over."""
 import numpy as np
