@@ -13,6 +13,36 @@ struct Fit {
   bool rag = false;
 };
 
+// Microseconds per sweep launch by launch, one sweep each: the launch, the
+// 64-cell pieces of rows (a wave's work) and the bytes.  Within 10 % (rms) of
+// 680 measured grids of 2 to 6000 columns, 1 to 4096 rows and 4 to 30000
+// levels.
+template <typename T>
+double one_sweep_us(const Grid &g, bool chebyshev) {
+  const bool f32 = sizeof(T) == 4;
+  const double pieces = 1e-3 * ((g.nx + 63) / 64) * g.ny * g.nz;
+  const double mb = 1e-6 * (double)g.n * sizeof(T) * (chebyshev ? 4 : 3);
+  if (g.ny == 1)
+    return f32 ? 3.5 + 0.072 * pieces + 0.094 * mb : 3.7 + 0.148 * pieces + 0.058 * mb;
+  return f32 ? 4.0 + 0.086 * pieces + 0.054 * mb : 4.0 + 0.202 * pieces + 0.041 * mb;
+}
+
+// Microseconds per sweep in boxes of a shape that hold so many levels per
+// thread: much the same whatever part of a box's columns and rows is filled
+// (within 8 %, rms, of 490 measured grids).  The small shapes, 0 here, were
+// nowhere more than 2 % slower than launch by launch.
+template <typename T>
+double resident_us(int shape, int levels) {
+  const bool f32 = sizeof(T) == 4;
+  switch (shape) {
+    case 3: return f32 ? 0.0 : 4.4 + 0.104 * levels;
+    case 4: return f32 ? 1.9 + 0.244 * levels : 5.2 + 0.357 * levels;
+    case 5: return 6.0 + 0.183 * levels;
+    case 7: return f32 ? 7.4 + 0.053 * levels : 7.7 + 0.053 * levels;
+    default: return 0.0;
+  }
+}
+
 // One block per CU: the boxes of shape B, if they all fit at once.
 template <class B>
 bool try_box(const Grid &g, int shape, Fit *f) {
@@ -36,7 +66,7 @@ bool try_box(const Grid &g, int shape, Fit *f) {
 // Fixed-weight Jacobi sweeps (small grids: their count grows with the square
 // of the grid's width) have no large boxes.
 template <typename T>
-Fit fit_of(const Grid &g, bool chebyshev) {
+Fit smallest_fit(const Grid &g, bool chebyshev) {
   static_assert(kResidentBlocks <= kNT, "every block's partial has a thread that reads it");
   using S = Shapes<T>;
   Fit f;
@@ -49,6 +79,20 @@ Fit fit_of(const Grid &g, bool chebyshev) {
     return f;
   if (S::F32) try_box<typename S::L>(g, 5, &f);
   return f;
+}
+
+// A grid that fills little of the large boxes (few columns or rows, so many
+// levels) is not worth a box's time: those run launch by launch.  Resident and
+// one by one, microseconds per sweep: 9.7 and 5.6 for one row, 8000 x 65 FP32,
+// 9.4 and 16.5 for 640 x 5120 FP64; 10.2 and 6.8 for 929 x 3 x 470 FP32, 12.6
+// and 20.1 for 114 x 343 x 160; 11.1 and 8.8 for 3 x 17 x 1470 FP64, 11.3 and
+// 22.0 for 1327 x 28 x 95.
+template <typename T>
+Fit fit_of(const Grid &g, bool chebyshev) {
+  const Fit f = smallest_fit<T>(g, chebyshev);
+  if (f.shape == 0) return f;
+  const int box = (g.nz + f.tz - 1) / f.tz, levels = g.ny == 1 ? (box + kNW - 1) / kNW : box;
+  return resident_us<T>(f.shape, levels) <= one_sweep_us<T>(g, chebyshev) ? f : Fit{};
 }
 
 }  // namespace

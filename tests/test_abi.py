@@ -229,3 +229,36 @@ int main(void) {
     with pytest.raises(lib.LesError):
         lib.solver_plan(lib.make_config(li.workload("C1", dt=0.0)))
     assert lib.load().les_solver_state(None, C.byref(I())) == lib.LES_ERR_ARG
+
+
+def grid_plan(lib, precision, scheme, nz, ny, nx, S=0):
+    p = li.workload("C1", nx=nx, ny=ny, nz=nz, precision=precision, poisson_scheme=scheme,
+                    sweeps_per_launch=S)
+    p["dz"] = min(p["dz"], 20000.0 / nz)  # below the adiabatic atmosphere's top
+    return lib.solver_plan(lib.make_config(p))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_resident_solves_only_where_boxes_are_used(lib, precision):
+    """Grids that fit the chip but leave most of its largest boxes empty take
+    longer resident than launch by launch."""
+    def blocks(scheme, *shape):
+        return grid_plan(lib, precision, scheme, *shape)["resident_blocks"]
+    cheb = "chebyshev"
+    # one row: tall and narrow, or too small for the largest boxes
+    for shape in ((20000, 1, 2), (8000, 1, 65), (14975, 1, 5), (621, 1, 819), (572, 1, 1146)):
+        assert blocks(cheb, *shape) == 0 and blocks("jacobi", *shape) == 0
+    for shape in ((640, 1, 5120), (500, 1, 4900)):
+        assert blocks(cheb, *shape) > 128
+    # a few rows or columns by many levels
+    if precision == "fp32":
+        empty, full = [(3127, 6, 105), (470, 3, 929), (4106, 3, 18), (7150, 10, 3)], \
+            [(160, 343, 114), (128, 256, 256), (1410, 28, 112), (60, 191, 243), (128, 1024, 4)]
+    else:
+        empty, full = [(1470, 17, 3), (1235, 2, 200)], [(95, 28, 1327), (64, 256, 256),
+                                                        (64, 1024, 24), (30, 1847, 5)]
+    assert [blocks(cheb, *s) for s in empty] == [0] * len(empty)
+    assert all(blocks(cheb, *s) > 0 for s in full)
+    # the small boxes always
+    for shape in ((4, 2, 2), (32, 32, 32), (64, 64, 64), (2000, 1, 24), (128, 1, 1024), (16, 500, 8)):
+        assert blocks(cheb, *shape) > 0 and blocks("jacobi", *shape) > 0
