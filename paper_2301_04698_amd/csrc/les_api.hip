@@ -596,7 +596,11 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
   };
   auto launch_at = [&](int mm) {
     Launch L{mm, 1, is_check(mm)};
-    // the sweeps up to the next check, in launches as equal as they come
+    // The sweeps up to the next check, in launches as equal as they come.
+    // Filled from the front instead (25 as 8 x 3 + 1, not 7 x 3 + 2 x 2) a
+    // sweep takes 137.5 us and not 145.5 at 512 x 512 x 256 FP32, but 68.2 and
+    // not 63.6 at 67 x 401 x 878 FP64 with fixed weights, 18.3 and not 17.5 at
+    // 571 x 511 x 26.
     int64_t left = max_sweeps - mm;
     if (fixed <= 0) left = std::min<int64_t>(left, every - mm % every);
     if (left > 1) {
