@@ -284,6 +284,9 @@ typedef struct les_solver_info {
                                 launch, as all later solves of the handle */
   int32_t refused;           /* resident launches that the runtime refused:
                                 as above */
+  int32_t tile_rows;         /* rows of a tile of several sweeps: 64 (FP64 32),
+                                or 4 on thin grids; 0: one sweep per launch */
+  int32_t reserved;
 } les_solver_info;
 
 #define LES_NPROFILES 9  /* thl, qt, ql, u, v, w, w^2, w^3, b (horizontal means) */

@@ -17,6 +17,8 @@
 // arithmetic alone takes 50 of the 126 us below.  512 x 512 x 256 FP32: 126 us
 // per sweep against 203 one by one (171 with one plane in flight instead of
 // two); 512 x 256 x 128 FP64 57 against 116.
+#include <algorithm>
+
 #include "les_column.h"
 #include "les_sweep.h"
 
@@ -276,6 +278,31 @@ int msweep_blocks(const Grid &g, int S) {
   return mshape_of(g, S, MTile<T>::BY).blocks;
 }
 
+// Microseconds of a launch of two sweeps: its start, the planes its rounds of
+// blocks walk and the cells, or the memory's time beyond the caches.  Within 20
+// % (rms) of the 219 grids of sweep2_us.
+template <typename T>
+double two_sweep_tiles_us(const Grid &g) {
+  const MShape m = mshape_of(g, 2, MTile<T>::BY);
+  const double planes = (double)((m.ntiles + 255) / 256) * (m.kc + 4);
+  const double cells = 1e-6 * (double)g.n;
+  const bool f32 = sizeof(T) == 4;
+  return std::max(f32 ? 2.4 + 1.52 * planes + 0.72 * cells : 1.5 + 1.28 * planes + 0.37 * cells,
+                  two_sweeps_streamed<T>(g) ? (f32 ? 4.0 : 8.3) * cells : 0.0);
+}
+
+// Rows of a tile.  Two sweeps run by tiles of 64 (FP64 32) rows here or by
+// four-row waves (k_sweep2.hip): whichever takes less, of those whose partials
+// fit (0: none, one sweep per launch).
+template <typename T>
+int msweep_rows(const Grid &g, int S) {
+  constexpr int BY = MTile<T>::BY;
+  if (S != 2) return S > 2 ? BY : 0;
+  const bool tiles = msweep_blocks<T>(g, 2) <= kPartials, thin = sweep2_blocks(g) > 0;
+  if (tiles && thin) return two_sweep_tiles_us<T>(g) <= sweep2_us<T>(g) ? BY : kThinRows;
+  return tiles ? BY : thin ? kThinRows : 0;
+}
+
 // Three sweeps a launch where a launch forms at most five cells per result
 // (tile rings, pipeline planes and a last round that is not full), else one
 // by one: thin grids and short rows leave most of a tile unused.  Per sweep,
@@ -285,8 +312,8 @@ int msweep_blocks(const Grid &g, int S) {
 // 33 x 44 FP32) 6.8 and 6.9; 10.4 (5120 x 8 x 640 FP32) 86 and 195.
 template <typename T>
 int msweep_depth(const Grid &g, int asked) {
-  if (asked > 1) return msweep_blocks<T>(g, asked) <= kPartials ? asked : 1;
-  if (asked == 1) return 1;
+  if (asked == 2 && msweep_rows<T>(g, 2) == 0) return 1;
+  if (asked > 0) return asked;
   constexpr int S = 3, BY = MTile<T>::BY;
   const MShape m = mshape_of(g, S, BY);
   const int64_t rounds = (m.ntiles + 255) / 256;
@@ -331,6 +358,7 @@ void launch_msweep(const Grid &g, int S, bool chebyshev, bool check, bool first,
 #define LES_INST(T)                                                                              \
   template int msweep_blocks<T>(const Grid &, int);                                              \
   template int msweep_depth<T>(const Grid &, int);                                               \
+  template int msweep_rows<T>(const Grid &, int);                                                \
   template void launch_msweep<T>(const Grid &, int, bool, bool, bool, double, const double *,    \
                                  const T *, const T *, T *, T *, const T *, SolveCtl *, double *, \
                                  hipStream_t);

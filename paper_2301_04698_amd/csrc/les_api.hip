@@ -229,6 +229,7 @@ struct les_handle {
   Thermo thermo;
   double mu_min, mu_max;
   int sweeps_per_launch;  // temporal blocking depth of the Poisson sweeps
+  int tile_rows;          // rows of its tiles (kThinRows: launch_sweep2)
   SolveCtl *ctl_host;  // pinned mirror for the final read-back
   int64_t *poll_word;      // pinned, coherent: (decision number << 32) | done, written
                            // by the kernel deciding each residual test
@@ -453,6 +454,8 @@ les_solver_info plan_of(const les_config *c) {
     p.resident_blocks = fp64 ? psweep_blocks<double>(g, cheb) : psweep_blocks<float>(g, cheb);
   p.sweeps_per_launch = fp64 ? msweep_depth<double>(g, c->sweeps_per_launch)
                              : msweep_depth<float>(g, c->sweeps_per_launch);
+  p.tile_rows = fp64 ? msweep_rows<double>(g, p.sweeps_per_launch)
+                     : msweep_rows<float>(g, p.sweeps_per_launch);
   return p;
 }
 
@@ -583,6 +586,7 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
   const bool cheb = c.poisson_scheme == LES_CHEBYSHEV;
   const auto [omega_j, rho] = sweep_weights(h);
   const int smax = h->sweeps_per_launch;
+  const bool thin = h->tile_rows == kThinRows;
   // Launches of up to smax sweeps, made one at a time; a residual check at
   // sweep m is computed by the launch that starts at m (its input iterate
   // is phi_m), so launches are cut at check positions.  Checks at every
@@ -723,6 +727,10 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
                        prev >= 0 ? buf[prev] : nullptr, buf[out_last], rhs, V.ctl, parts,
                        decides ? pend_parts : nullptr, decides ? pend_np : 0,
                        decides ? pend_m : -1, decides ? h->poll_word_dev : nullptr, next_seq(), s);
+    else if (thin)
+      launch_sweep2<T>(g, cheb, L.check, L.m == 0, omega_j, wc, buf[cur],
+                       prev >= 0 ? buf[prev] : nullptr, buf[out_last], buf[out_prev], rhs, V.ctl,
+                       parts, s);
     else
       launch_msweep<T>(g, L.S, cheb, L.check, L.m == 0, omega_j, wc, buf[cur],
                        prev >= 0 ? buf[prev] : nullptr, buf[out_last], buf[out_prev], rhs, V.ctl,
@@ -749,7 +757,8 @@ int run_sweeps(les_handle *h, View<T> &V, const T *rhs, int fixed, int cap, Solv
       ++nchecks;
       // partial sums come from this launch's own block decomposition; the
       // next launch decides if both are one-sweep launches
-      const int np = L.S == 1 ? tsweep_blocks(g, sizeof(T) == 8) : msweep_blocks<T>(g, L.S);
+      const int np = L.S == 1 ? tsweep_blocks(g, sizeof(T) == 8)
+                              : (thin ? sweep2_blocks(g) : msweep_blocks<T>(g, L.S));
       if (L.S == 1 && has_next && nextL.S == 1) {
         pend_m = L.m;
         pend_parts = parts;
@@ -1480,7 +1489,9 @@ int init_impl(const les_config *cfg, const les_buffers *bufs, void *stream, les_
   h->steps_done = 0;
   h->resident = resident_fits(h);
   h->tag = 1;
-  h->sweeps_per_launch = plan_of(cfg).sweeps_per_launch;
+  const les_solver_info plan = plan_of(cfg);
+  h->sweeps_per_launch = plan.sweeps_per_launch;
+  h->tile_rows = plan.tile_rows;
   std::memset(&h->ran, 0, sizeof(h->ran));
   h->fault = LES_FAULT_NONE;
   h->fault_after = 0;
@@ -1666,6 +1677,7 @@ int les_solver_state(const les_handle *h, les_solver_info *out) {
   *out = h->ran;
   out->resident_blocks = h->resident ? p.resident_blocks : 0;
   out->sweeps_per_launch = h->sweeps_per_launch;
+  out->tile_rows = h->tile_rows;
   return LES_OK;
 }
 

@@ -87,9 +87,23 @@ int tsweep_blocks(const Grid &g, bool is_double);
 template <typename T>
 int msweep_blocks(const Grid &g, int S);
 // Sweeps per launch of a solve launch by launch: what the configuration asks
-// for (where a launch's residual partials fit), or the kernel's own choice (0).
+// for (one where a launch's residual partials do not fit), or the kernel's own
+// choice (0).
 template <typename T>
 int msweep_depth(const Grid &g, int asked);
+// Rows of a tile of S sweeps at once: kThinRows is launch_sweep2 (S = 2), else
+// launch_msweep (0: neither).
+constexpr int kThinRows = 4;
+template <typename T>
+int msweep_rows(const Grid &g, int S);
+int sweep2_blocks(const Grid &g);  // 0: its partials do not fit
+template <typename T>
+double sweep2_us(const Grid &g);
+// The five arrays of a launch of two sweeps exceed the Infinity Cache.
+template <typename T>
+bool two_sweeps_streamed(const Grid &g) {
+  return 5.0 * sizeof(T) * (double)g.n > 256e6;
+}
 
 // ------------------------------------------------------------ launchers
 template <typename T>
@@ -205,6 +219,12 @@ void launch_tsweep(const Grid &g, bool chebyshev, bool check, bool first, double
 // partials).
 template <typename T>
 void launch_msweep(const Grid &g, int S, bool chebyshev, bool check, bool first, double omega_jacobi,
+                   const double *omega_cheb, const T *cur, const T *prev, T *out_last, T *out_prev,
+                   const T *rhs, SolveCtl *ctl, double *partials, hipStream_t s);
+
+// The same with S = 2 for thin grids (sweep2_blocks partials).
+template <typename T>
+void launch_sweep2(const Grid &g, bool chebyshev, bool check, bool first, double omega_jacobi,
                    const double *omega_cheb, const T *cur, const T *prev, T *out_last, T *out_prev,
                    const T *rhs, SolveCtl *ctl, double *partials, hipStream_t s);
 

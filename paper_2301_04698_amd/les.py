@@ -111,11 +111,12 @@ class LesStepStats(C.Structure):
 class LesSolverInfo(C.Structure):
     _fields_ = [("resident_blocks", C.c_int32), ("sweeps_per_launch", C.c_int32),
                 ("resident_passes", C.c_int64), ("launches", C.c_int64 * 3),
-                ("gave_up", C.c_int32), ("refused", C.c_int32)]
+                ("gave_up", C.c_int32), ("refused", C.c_int32), ("tile_rows", C.c_int32),
+                ("reserved", C.c_int32)]
 
     def as_dict(self):
         return {n: list(v) if n == "launches" else v
-                for n, v in ((n, getattr(self, n)) for n, _ in self._fields_)}
+                for n, v in ((n, getattr(self, n)) for n, _ in self._fields_ if n != "reserved")}
 
 
 class LesDiag(C.Structure):

@@ -214,14 +214,14 @@ def test_solver_info_layout_and_plan(lib, tmp_path):
 #include <stddef.h>
 int main(void) {
   printf("%zu %zu %zu\n", sizeof(les_solver_info), offsetof(les_solver_info, launches),
-         offsetof(les_solver_info, refused));
+         offsetof(les_solver_info, tile_rows));
   return 0;
 }''')
     exe = tmp_path / "si"
     subprocess.run(["gcc", "-I", os.path.join(ROOT, "include"), str(prog), "-o", str(exe)], check=True)
     got = [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True).stdout.split()]
     I = lib.LesSolverInfo
-    assert got == [C.sizeof(I), I.launches.offset, I.refused.offset]
+    assert got == [C.sizeof(I), I.launches.offset, I.tile_rows.offset]
     plan = lib.solver_plan(lib.make_config(li.workload("C1", nx=64, ny=64, nz=64, precision="fp32")))
     assert plan["resident_blocks"] == 128 and plan["launches"] == [0, 0, 0]
     plan = lib.solver_plan(lib.make_config(li.workload("C1", sweeps_per_launch=1)))
@@ -262,3 +262,24 @@ def test_resident_solves_only_where_boxes_are_used(lib, precision):
     # the small boxes always
     for shape in ((4, 2, 2), (32, 32, 32), (64, 64, 64), (2000, 1, 24), (128, 1, 1024), (16, 500, 8)):
         assert blocks(cheb, *shape) > 0 and blocks("jacobi", *shape) > 0
+
+
+def test_two_sweeps_per_launch_by_the_shape(lib):
+    """A caller's two sweeps per launch run in tall tiles where the grid fills
+    them, in four-row waves on thin grids, and one by one where no launch of
+    two has room for its residual sums."""
+    def rows(precision, *shape):
+        plan = grid_plan(lib, precision, "chebyshev", *shape, S=2)
+        return plan["sweeps_per_launch"], plan["tile_rows"]
+    for shape in ((640, 1, 5120), (128, 1, 1024), (640, 8, 5120), (300, 20, 2000), (438, 4, 2037)):
+        assert rows("fp32", *shape) == (2, 4)
+    for shape in ((640, 1, 5120), (640, 8, 5120), (433, 1, 4315)):
+        assert rows("fp64", *shape) == (2, 4)
+    for shape in ((256, 512, 512), (128, 256, 256), (4, 2500, 1700)):
+        assert rows("fp32", *shape) == (2, 64)
+    for shape in ((128, 256, 512), (60, 75, 100), (32, 32, 32)):
+        assert rows("fp64", *shape) == (2, 32)
+    assert rows("fp32", 4, 8192, 16384) == (2, 64)
+    assert rows("fp32", 4, 16384, 16384) == (1, 0)
+    assert rows("fp64", 4, 16384, 16384) == (1, 0)
+    assert rows("fp32", 4, 1, 1 << 29) == (1, 0)
