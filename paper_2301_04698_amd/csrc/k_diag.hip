@@ -18,13 +18,25 @@ struct DiagSums {
 };
 constexpr int kDiagParts = 13;  // values of a part of a level
 
-// blockIdx.x: part of level blockIdx.y's rows.  A wave takes a row at a time,
-// so that a cell's indices need no division; the sums run over a fixed order
-// and are deterministic.  Bound by memory, 7 fields read once: 256 x 256 x 128
-// FP32 63 us (74 with two barriers per value summed); with one block per level
-// (128 of 256 CUs, a 64-bit division per cell) it took 289 us.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, Profiles<T> P,
+// How a level is split.  A wave takes a unit at a time: a row, or where rows
+// are fewer than waves one of the `pieces` of a row (`len` columns each), or
+// where a row leaves more than half of the lanes idle the 64 / width rows that
+// it holds side by side.
+struct DiagSplit {
+  int width;       // lanes of a row, a power of two: 64, or the least that hold a narrow row
+  int pieces, len;
+  int units, parts;  // of a level: units, blocks
+};
+
+// blockIdx.x: part of level blockIdx.y's units.  A cell's indices need no
+// division; the sums run over a fixed order and are deterministic.  Bound by
+// memory, 7 fields read once: 256 x 256 x 128 FP32 63 us (74 with two barriers
+// per value summed); with one block per level (128 of 256 CUs, a 64-bit
+// division per cell) it took 289 us.  With whole rows only, the call took 1795
+// us at 51200 x 1 x 16 FP64 (359 with one block per level), 309 (180) at 5120 x
+// 1 x 640, 81 (61) at 4 x 2048 x 64 FP32; with these units 62, 167 and 40.
+template <typename T, bool NARROW>
+__global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, DiagSplit sp, Profiles<T> P,
                                                       const T *__restrict__ u,
                                                       const T *__restrict__ v,
                                                       const T *__restrict__ w,
@@ -37,8 +49,8 @@ __global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, Profiles<T> P,
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int kp = min(k + 1, g.nz - 1), km = max(k - 1, 0);
   // w changes sign across the walls
-  const double sp = k + 1 < g.nz ? 1.0 : -1.0, sm = k > 0 ? 1.0 : -1.0;
-  const double r0 = P.rho0[k], rm = P.rho0[km] * sm, rp = P.rho0[kp] * sp;
+  const double up = k + 1 < g.nz ? 1.0 : -1.0, dn = k > 0 ? 1.0 : -1.0;
+  const double r0 = P.rho0[k], rm = P.rho0[km] * dn, rp = P.rho0[kp] * up;
   const double hx = 0.5 / g.dx, hy = 0.5 / g.dy, hz = 0.5 / g.dz;
   const double cx = g.dt / g.dx, cy = g.dt / g.dy, cz = g.dt / g.dz;
   DiagSums a;
@@ -47,11 +59,23 @@ __global__ __launch_bounds__(kBlock) void diag_kernel(Grid g, Profiles<T> P,
   a.dmax = a.cmax = 0.0;
   constexpr int NW = kBlock / 64;
   const int64_t lev = g.nxy * k;
-  for (int j = (int)blockIdx.x * NW + wave; j < g.ny; j += (int)gridDim.x * NW) {
+  for (int n = (int)blockIdx.x * NW + wave; n < sp.units; n += (int)gridDim.x * NW) {
+    int j, i0, i1;
+    if (NARROW) {
+      j = n * (64 / sp.width) + lane / sp.width;
+      i0 = lane & (sp.width - 1);
+      i1 = j < g.ny ? g.nx : 0;
+      j = min(j, g.ny - 1);
+    } else {
+      j = n / sp.pieces;
+      i0 = (n - j * sp.pieces) * sp.len;
+      i1 = min(g.nx, i0 + sp.len);
+      i0 += lane;
+    }
     const int64_t row = lev + g.sy * j;
     const int64_t yp = lev + g.sy * pwrap(j + 1, g.ny), ym = lev + g.sy * pwrap(j - 1, g.ny);
     const int64_t zp = g.nxy * kp + g.sy * j, zm = g.nxy * km + g.sy * j;
-    for (int i = lane; i < g.nx; i += 64) {
+    for (int i = i0; i < i1; i += 64) {
       const int64_t q = row + i;
       const int ip = pwrap(i + 1, g.nx), im = pwrap(i - 1, g.nx);
       const double uu = u[q], vv = v[q], ww = w[q];
@@ -118,22 +142,37 @@ __global__ __launch_bounds__(64) void diag_final_kernel(Profiles<T> P, int npart
 
 }  // namespace
 
-// Parts of a level: four blocks on each CU (eight: 4 us more at 256 x 256 x
-// 128), rows for each of a block's waves.
-static int diag_parts(const Grid &g) {
-  const int rows = (g.ny + kBlock / 64 - 1) / (kBlock / 64);
-  return std::max(1, std::min(rows, (1023 + g.nz) / g.nz));
+// Four blocks on each CU (eight: 4 us more at 256 x 256 x 128), and units for
+// each of a block's waves.
+static DiagSplit diag_split(const Grid &g) {
+  constexpr int NW = kBlock / 64;
+  const int most = (1023 + g.nz) / g.nz;
+  DiagSplit d;
+  d.width = 64;
+  while (d.width >= 2 * g.nx) d.width /= 2;
+  const int blocks = (g.nx + 63) / 64;  // of 64 columns
+  const int want = std::min(blocks, std::max(1, most * NW / g.ny));
+  d.len = (blocks + want - 1) / want * 64;
+  d.pieces = (g.nx + d.len - 1) / d.len;
+  const int rows = 64 / d.width;  // side by side
+  d.units = (g.ny + rows - 1) / rows * d.pieces;
+  d.parts = std::min((d.units + NW - 1) / NW, most);
+  return d;
 }
 
-size_t diag_part_values(const Grid &g) { return (size_t)g.nz * diag_parts(g) * kDiagParts; }
+size_t diag_part_values(const Grid &g) { return (size_t)g.nz * diag_split(g).parts * kDiagParts; }
 
 template <typename T>
 void launch_diag(const Grid &g, const Profiles<T> &P, const T *u, const T *v, const T *w,
                  const T *thl, const T *qt, const T *ql, const T *b, double *parts,
                  double *level_sums, hipStream_t s) {
-  const int n = diag_parts(g);
-  diag_kernel<T><<<dim3(n, g.nz), kBlock, 0, s>>>(g, P, u, v, w, thl, qt, ql, b, parts);
-  diag_final_kernel<T><<<g.nz, 64, 0, s>>>(P, n, parts, level_sums);
+  const DiagSplit d = diag_split(g);
+  const dim3 grid(d.parts, g.nz);
+  if (d.width < 64)
+    diag_kernel<T, true><<<grid, kBlock, 0, s>>>(g, d, P, u, v, w, thl, qt, ql, b, parts);
+  else
+    diag_kernel<T, false><<<grid, kBlock, 0, s>>>(g, d, P, u, v, w, thl, qt, ql, b, parts);
+  diag_final_kernel<T><<<g.nz, 64, 0, s>>>(P, d.parts, parts, level_sums);
 }
 
 #define LES_INST(T)                                                                            \
