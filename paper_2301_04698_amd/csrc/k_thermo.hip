@@ -109,7 +109,9 @@ __device__ CellState saturation_adjust(const Thermo &c, double thl, double qt, d
   return CellState{tb, rb.ph.ql, rb.ph.qi, exp(rb.ln_pi)};
 }
 
-template <typename T>
+// LEVELS: per_level blocks to a level, so that its index and profile values are
+// uniform; else the blocks take the cells in order, across levels.
+template <typename T, bool LEVELS>
 __global__ __launch_bounds__(kBlock) void thermo_kernel(Grid g, Thermo c, Profiles<T> P,
                                                         const T *__restrict__ thl_a,
                                                         const T *__restrict__ qt_a,
@@ -120,11 +122,18 @@ __global__ __launch_bounds__(kBlock) void thermo_kernel(Grid g, Thermo c, Profil
                                                         T *__restrict__ ql, T *__restrict__ cpmpi,
                                                         T *__restrict__ Tout,
                                                         unsigned per_level) {
-  // per_level blocks to a level: its index and profile values are uniform
-  const int k = (int)(blockIdx.x / per_level);
-  const int64_t r = (int64_t)(blockIdx.x - k * per_level) * blockDim.x + threadIdx.x;
-  if (r >= g.nxy) return;
-  const int64_t q = r + g.nxy * k;
+  int k;
+  int64_t q;
+  if (LEVELS) {
+    k = (int)(blockIdx.x / per_level);
+    q = (int64_t)(blockIdx.x - k * per_level) * blockDim.x + threadIdx.x;
+    if (q >= g.nxy) return;
+    q += g.nxy * k;
+  } else {
+    q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= g.n) return;
+    k = (int)(q / g.nxy);
+  }
   T th = thl_a[q], qw = qt_a[q];
   if (thl_b) {
     // state midway between sub-iterate k and the step-start scalars
@@ -254,6 +263,16 @@ __global__ __launch_bounds__(kBlock) void average_kernel(int64_t n, const T *__r
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
+// Blocks of their own for each level where that leaves at most one thread in
+// 64 idle, or where the whole launch is two blocks on a CU (eight if a level is
+// a wave).  By levels and in order: 256 x 256 x 128 FP32 313 and 316 us; 17 x 17
+// x 2000 64 and 51, 4 x 4 x 60000 239 and 71, 100 x 75 x 60 34 and 32; 9 x 9 x
+// 400 29 and 34, 33 x 1 x 1000 25 and 34.
+inline bool whole_levels(const Grid &g, unsigned per_level) {
+  return (int64_t)per_level * kBlock - g.nxy <= g.nxy / 64 ||
+         (int64_t)per_level * g.nz <= (g.nxy <= 64 ? 2048 : 512);
+}
+
 }  // namespace
 
 template <typename T>
@@ -261,8 +280,12 @@ void launch_thermo(const Grid &g, const Thermo &c, const Profiles<T> &P, const T
                    const T *qt_a, const T *thl_b, const T *qt_b, T *thl_mid, T *qt_mid, T *b,
                    T *ql, T *cpmpi, T *Tout, hipStream_t s) {
   const unsigned per_level = blocks_for(g.nxy);
-  thermo_kernel<T><<<per_level * (unsigned)g.nz, kBlock, 0, s>>>(
-      g, c, P, thl_a, qt_a, thl_b, qt_b, thl_mid, qt_mid, b, ql, cpmpi, Tout, per_level);
+  if (whole_levels(g, per_level))
+    thermo_kernel<T, true><<<per_level * (unsigned)g.nz, kBlock, 0, s>>>(
+        g, c, P, thl_a, qt_a, thl_b, qt_b, thl_mid, qt_mid, b, ql, cpmpi, Tout, per_level);
+  else
+    thermo_kernel<T, false><<<blocks_for(g.n), kBlock, 0, s>>>(
+        g, c, P, thl_a, qt_a, thl_b, qt_b, thl_mid, qt_mid, b, ql, cpmpi, Tout, 0);
 }
 
 template <typename T>
