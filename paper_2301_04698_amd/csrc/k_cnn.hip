@@ -1276,8 +1276,15 @@ __global__ __launch_bounds__(kWgradEdgeNT<CI>) void wgrad_edge_kernel(
 
 // Sums of the blocks' partials: eight threads per entry, each a run of the
 // blocks, then their sums in order.
+// LAST: the products above multiply a cell's activation also by zero, for the
+// taps that no output reads it through (beside the edges and walls).  That is
+// nothing unless the activation is not finite, so a weight's gradient that came
+// out not finite is summed again from the outputs, by the taps that read.
+template <bool LAST>
 __global__ __launch_bounds__(kBlock) void wgrad_final_kernel(const double *__restrict__ partials,
-                                                             int E, int nw,
+                                                             int E, int nw, CnnGeom G,
+                                                             const float *__restrict__ gy,
+                                                             const uint16_t *__restrict__ ain,
                                                              float *__restrict__ gw,
                                                              float *__restrict__ gb) {
   constexpr int P = 8, N = kBlock / P;
@@ -1292,12 +1299,30 @@ __global__ __launch_bounds__(kBlock) void wgrad_final_kernel(const double *__res
   }
   red[part][le] = s;
   __syncthreads();
-  if (part != 0 || e >= E) return;
-  for (int m = 1; m < P; ++m) s += red[m][le];
-  if (e < nw)
-    gw[e] = (float)s;
-  else
-    gb[e - nw] = (float)s;
+  if (part == 0 && e < E) {
+    for (int m = 1; m < P; ++m) s += red[m][le];
+    if (e < nw)
+      gw[e] = (float)s;
+    else
+      gb[e - nw] = (float)s;
+    red[0][le] = s;
+  }
+  if constexpr (LAST) {
+    __syncthreads();
+    for (int l = 0; l < N; ++l) {  // uniform over the block
+      const int w = blockIdx.x * N + l, t = w / kCnnCh, ch = w % kCnnCh;
+      if (w >= nw || isfinite(red[0][l])) continue;
+      double v = 0.0;
+      for (int64_t q = threadIdx.x; q < G.n_out; q += kBlock) {
+        const Cell c = decode(q, G.nz, G.nyo, G.nxo);
+        const int k = min(max(c.k + t / 9 - 1, 0), G.nz - 1);
+        const int64_t src = (((int64_t)c.b * G.nz + k) * G.nyi + c.j + t / 3 % 3) * G.nxi + c.i + t % 3;
+        v += (double)gy[q] * (double)bf2f(ain[src * kCnnCh + ch]);
+      }
+      v = block_sum(v);
+      if (threadIdx.x == 0) gw[w] = (float)v;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void adam_kernel(int n, float *__restrict__ p,
@@ -1604,9 +1629,11 @@ void launch_cnn_wgrad(int layer, const CnnGeom &G, const float *gy, const uint16
     wgrad_edge_kernel<1, true><<<kCnnWgradBlocks, kWgradEdgeNT<1>, 0, s>>>(G, gy, ain, partials);
   else
     wgrad_mid_kernel<<<kCnnWgradBlocks, kWgradNT, 0, s>>>(G, gy, ain, partials);
-  wgrad_final_kernel<<<(E + 31) / 32, kBlock, 0, s>>>(partials, E, nw,
-                                                     grad + cnn_weight_offset(G.inputs, layer),
-                                                     grad + cnn_bias_offset(G.inputs, layer));
+  float *gw = grad + cnn_weight_offset(G.inputs, layer), *gb = grad + cnn_bias_offset(G.inputs, layer);
+  if (co == 1)
+    wgrad_final_kernel<true><<<(E + 31) / 32, kBlock, 0, s>>>(partials, E, nw, G, gy, ain, gw, gb);
+  else
+    wgrad_final_kernel<false><<<(E + 31) / 32, kBlock, 0, s>>>(partials, E, nw, G, gy, ain, gw, gb);
 }
 
 void launch_cnn_adam(int n, float *params, const float *grad, float *m, float *v, int step,

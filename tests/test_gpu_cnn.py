@@ -575,3 +575,28 @@ def test_backward_at_the_edges_of_its_tiles(gpu, shape):
         e = b + (16 if l < 3 else 1)
         assert rel(got[a:b], ref[a:b]) <= 1e-5, (l, rel(got[a:b], ref[a:b]))
         assert rel(got[b:e], ref[b:e]) <= 1e-5, (l, "bias")
+
+
+@pytest.mark.parametrize("where", [(0, 0, 0), (5, 0, 13), (2, 12, 0), (3, 6, 7)])
+def test_backward_keeps_nonfinite_activations_to_their_taps(gpu, where):
+    """An overflowed input reaches the last layer's input beside an edge of the
+    crop; only the taps that read it there have a non-finite gradient."""
+    from oracle import cnn as ocnn
+    p = params(32)
+    rng = np.random.default_rng(33)
+    x = rng.standard_normal((1, 6, 13, 14)).astype(np.float32).astype(float)
+    x[0][where] = np.inf
+    P = _t(p)
+    packed = gpu.pack(P)
+    out, work = gpu.forward(P, packed, _t(x), periodic=False, alpha=0.1)
+    acts = [np.ascontiguousarray(_np(gpu.stored_input(x.shape, work, l, alpha=0.1)))
+            for l in range(4)]
+    assert all((~np.isfinite(a)).any() for a in acts)
+    gout = rng.standard_normal(_np(out).shape).astype(np.float32).astype(float)
+    ref = ocnn.backward(p, x, acts, [acts[1], acts[2], acts[3]], gout, periodic=False, alpha=0.1)
+    got = _np(gpu.backward(x.shape, packed, work, _t(gout), alpha=0.1))
+    ok = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), ok), (ok.sum(), np.isfinite(got).sum())
+    # the last layer's (the slope at a NaN, which the others need, is not defined)
+    m = ok[ocnn.weight_offset(3):]
+    assert rel(got[ocnn.weight_offset(3):][m], ref[ocnn.weight_offset(3):][m]) <= 1e-5
