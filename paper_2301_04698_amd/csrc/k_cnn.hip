@@ -1308,7 +1308,7 @@ __global__ __launch_bounds__(kBlock) void wgrad_final_kernel(const double *__res
     red[0][le] = s;
   }
   if constexpr (LAST) {
-    __syncthreads();
+    if (!__syncthreads_or(part == 0 && e < nw && !isfinite(s))) return;
     for (int l = 0; l < N; ++l) {  // uniform over the block
       const int w = blockIdx.x * N + l, t = w / kCnnCh, ch = w % kCnnCh;
       if (w >= nw || isfinite(red[0][l])) continue;
