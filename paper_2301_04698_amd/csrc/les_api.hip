@@ -895,6 +895,10 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
             timing->seconds += ms * 1e-3;
             timing->sweeps += r.stop_m + 1;
           }
+          // (a right-hand side that is zero or not finite ends a fixed count at
+          // sweep 0, which run_sweeps refuses too)
+          if (fixed > 0 && r.stop_m != fixed)
+            return fail(LES_ERR_STATE, "Poisson solve stopped at an unchecked sweep");
           if (r.done == 2) return fail(LES_ERR_NONFINITE, "non-finite Poisson residual");
           res2 = V.vert || (gs && r.guess_kept) ? r.res_out2 : r.res_norm2;
           return LES_OK;

@@ -137,3 +137,29 @@ def test_thin_two_sweep_launches_bitwise_equal(gpu, precision, scheme, shape):
         assert np.array_equal(a[0].cpu().numpy(), b[0].cpu().numpy())
         assert [a[1][k] for k in ("sweeps", "status")] == [b[1][k] for k in ("sweeps", "status")]
         assert b[1]["res_norm"] == pytest.approx(a[1]["res_norm"], rel=1e-12)
+
+
+@pytest.mark.parametrize("scheme,mean_mode", [("chebyshev", "exact"), ("jacobi", "swept")])
+@pytest.mark.parametrize("rhs", ["zero", "constant", "nan", "inf"])
+def test_fixed_count_without_a_right_hand_side_is_refused_either_way(gpu, rhs, scheme, mean_mode):
+    """A fixed number of sweeps on a right-hand side that is nothing, or not
+    finite: the same refusal resident and launch by launch; to the tolerance
+    the first is solved by nothing."""
+    import torch
+    shape = (6, 10, 70)
+    f = np.full(shape, {"zero": 0.0, "constant": 3.0}.get(rhs, 1.0))
+    if rhs in ("nan", "inf"):
+        f[2, 3, 4] = float(rhs)
+    for S in (1, 2, 0):
+        sim = gpu.LES(workload("fp32", scheme, shape, mean_mode=mean_mode, sweeps_per_launch=S))
+        with pytest.raises(gpu.LesError) as e:
+            sim.poisson_solve(torch.from_numpy(f), fixed_sweeps=5)
+        assert e.value.code == gpu.LES_ERR_STATE
+        if rhs in ("nan", "inf"):
+            with pytest.raises(gpu.LesError) as e:
+                sim.poisson_solve(torch.from_numpy(f))
+            assert e.value.code == gpu.LES_ERR_NONFINITE
+        else:
+            phi, st, rc = sim.poisson_solve(torch.from_numpy(f))
+            assert rc == 0 and st["sweeps"] == 0 and not phi.any()
+        sim.close()
