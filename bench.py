@@ -86,19 +86,18 @@ def run_sweeps(args):
 
     p = li.workload(args.workload, sweeps_per_launch=args.sweeps_per_launch)
     shape = (p["nz"], p["ny"], p["nx"])
-    n = p["nx"] * p["ny"] * p["nz"]
     sim = les.LES(p, device="cuda:0")
     dt = torch.float32 if p["precision"] == "fp32" else torch.float64
     rhs = torch.from_numpy(li.random_field(shape, seed=3)).to("cuda:0", dt)
     sim.poisson_solve(rhs, fixed_sweeps=10)
+    before = sim.solver_state()
     _, st, _ = sim.poisson_solve(rhs, fixed_sweeps=args.sweeps)
     per = st["seconds"] / args.sweeps
-    bpc = sweep_bytes_per_cell(p)
     print(json.dumps({
         "mode": "sweeps", "workload": args.workload, "grid": [p["nx"], p["ny"], p["nz"]],
         "precision": p["precision"], "scheme": p["poisson_scheme"], "sweeps": args.sweeps,
-        "us_per_sweep": per * 1e6, "bytes_per_sweep": bpc * n,
-        "form": sweep_form(p)[0], "algorithmic_GBs": bpc * n / per / 1e9, "frac_of_8TBs": bpc * n / per / 1e9 / HBM_PEAK_GBS,
+        "us_per_sweep": per * 1e6,
+        "roofline": sweep_roofline(p, per, solver_runs(before, sim.solver_state())),
         "note": "solve time includes rhs centring and the final residual check"}), flush=True)
 
 
@@ -121,42 +120,27 @@ def run_copy(args):
                       "us_per_copy": s * 1e6, "GBs_read_plus_write": 8 * n / s / 1e9}), flush=True)
 
 
-def _ceil(a, b):
-    return -(-a // b)
+def solver_runs(before, after):
+    """How the solves between two reports of a handle (LES.solver_state) ran:
+    (passes resident on the chip, launches of one, two and three sweeps, rows
+    of a tile of several)."""
+    if after["gave_up"] or after["refused"]:
+        progress(f"resident solves gave up a wait {after['gave_up']} and were refused "
+                 f"{after['refused']} times; solves run launch by launch since")
+    return (after["resident_passes"] - before["resident_passes"],
+            [b - a for a, b in zip(before["launches"], after["launches"])], after["tile_rows"])
 
 
-def sweep_form(p):
-    """How the library runs the sweeps of a solve on p's grid: ("resident",
-    all of them), ("several", 2 or 3 per launch) or ("single", 1).  The rules
-    are those of k_psweep.hip and k_msweep.hip."""
-    nx, ny, nz = p["nx"], p["ny"], p["nz"]
-    f32, cheb = p["precision"] == "fp32", p["poisson_scheme"] == "chebyshev"
-    by = 64 if f32 else 32  # rows of a tile of several sweeps
-    asked = p.get("sweeps_per_launch", 0)
-    if asked:
-        return ("single", 1) if asked == 1 else ("several", asked)
-    if ny == 1:
-        boxes = [(1, 32), (1, 256)]
-    else:
-        boxes = [(8, 4), (8, 8), (16, 8) if f32 else (8, 16)]
-        if cheb:
-            boxes += [(16, 16)] + ([(16, 32)] if f32 else [])
-    if any(_ceil(nx, 64) * _ceil(ny, r) * _ceil(nz, z) <= 256 for r, z in boxes):
-        return "resident", None
-    cols = _ceil(nx, 58) * _ceil(ny, by - 6)
-    cost = min(_ceil(cols * n, 256) * (_ceil(nz, n) + 6) for n in range(1, min(nz, 64) + 1))
-    return ("several", 3) if cost * 256 * 64 * by <= 5 * nx * ny * nz else ("single", 1)
-
-
-def sweep_roofline(p, avg_sweep):
-    """What the plain sweeps reach against what bounds them, from the average
-    seconds of one of them."""
-    form, S = sweep_form(p)
+def sweep_roofline(p, avg_sweep, runs):
+    """What the sweeps reach against what bounds them, from the average
+    seconds of one of them and the way they ran (solver_runs)."""
+    _, launches, rows = runs
     ncell = p["nx"] * p["ny"] * p["nz"]
     es = 8 if p["precision"] == "fp64" else 4
     cheb = p["poisson_scheme"] == "chebyshev"
     T = "double" if es == 8 else "float"
-    if form == "resident":
+    made = sum(launches)
+    if not made:  # every pass resident
         # the iterates never leave the chip: 3 + 1 + 6 + 1 + 2 (Chebyshev: + 3)
         # FP64 operations per cell, an FMA as two, and two of the residual's sum
         flops = (18 if cheb else 15) * ncell
@@ -169,18 +153,23 @@ def sweep_roofline(p, avg_sweep):
             "note": ("iterates in registers, right-hand side in LDS for the whole solve; one sweep "
                      f"per launch would move {sweep_bytes_per_cell(p) * ncell / 1e6:.0f} MB"),
         }
-    # one sweep: sweep_bytes_per_cell; several: 3 arrays in, 2 out
-    bytes_launch = (sweep_bytes_per_cell(p) if S == 1 else 5 * es) * ncell
-    achieved = bytes_launch / (avg_sweep * S) / 1e9
-    name = f"sweep1_kernel<{T}>" if S == 1 else f"msweep_kernel<{T}, {S}>"
+    # one sweep: sweep_bytes_per_cell; several: 3 arrays in, 2 out (1: Jacobi)
+    several = (5 if cheb else 3) * es
+    sweeps = sum((q + 1) * n for q, n in enumerate(launches))
+    bytes_sweep = (sweep_bytes_per_cell(p) * launches[0] + several * sum(launches[1:])) / sweeps * ncell
+    achieved = bytes_sweep / avg_sweep / 1e9
+    most = max(range(3), key=lambda q: launches[q]) + 1
+    name = (f"sweep1_kernel<{T}>" if most == 1 else f"sweep2_kernel<{T}>" if rows == 4
+            else f"msweep_kernel<{T}, {most}>")
     return {
-        "bound": "hbm", "kernel": name, "achieved": achieved, "peak": HBM_PEAK_GBS,
-        "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "avg_sweep_us": avg_sweep * 1e6,
-        "sweeps_per_launch": S, "avg_launch_us": avg_sweep * S * 1e6,
-        "bytes_per_launch": bytes_launch,
-        "note": (f"bytes a launch cannot do without, {bytes_launch / 1e6:.0f} MB, "
-                 + ("inside" if bytes_launch < 256e6 else "beyond")
-                 + " the 256 MB Infinity Cache"),
+        "bound": "hbm", "kernel": name,
+        "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
+        "avg_sweep_us": avg_sweep * 1e6, "launches_by_sweeps": launches,
+        "sweeps_per_launch": sweeps / made, "avg_launch_us": avg_sweep * sweeps / made * 1e6,
+        "bytes_per_sweep": bytes_sweep,
+        "note": (f"bytes that the launches made cannot do without, {bytes_sweep / 1e6:.0f} MB per "
+                 "sweep; launches counted over all of the solves, sweeps timed between residual "
+                 "tests"),
     }
 
 
@@ -363,6 +352,7 @@ def largest_domain(args):
 
     def timed(sim):
         torch.cuda.synchronize()
+        before = sim.solver_state()
         t0 = time.perf_counter()
         rc, st, recs = sim.step(T, records=True, time_sweeps=True)
         torch.cuda.synchronize()
@@ -379,7 +369,7 @@ def largest_domain(args):
             "starts": [r["guess"] for r in recs],
             "not_converged": st["not_converged"],
             "res_rel_max": st["res_rel_max"],
-        }, st
+        }, st, solver_runs(before, sim.solver_state())
 
     t0 = time.perf_counter()
     sim = les.LES(dict(p, guess="learned", guess_passes=args.guess_passes), li.initial_state(p),
@@ -397,7 +387,7 @@ def largest_domain(args):
     t_warm = time.perf_counter() - t0
     snap = {k: v.clone() for k, v in sim.fields.items()}
     _, pbar = sim.pressure()
-    learned, _ = timed(sim)
+    learned = timed(sim)[0]
     progress(f"1024x1024x256: learned form {learned['ms_per_step'] / 1e3:.1f} s/step, solves "
              f"{learned['sweeps_per_solve']} sweeps, starts {learned['starts']}")
     sim.close()
@@ -405,7 +395,7 @@ def largest_domain(args):
     torch.cuda.empty_cache()
     sim = les.LES(p, snap, device="cuda:0", pbar=pbar)
     del snap
-    plain, st = timed(sim)
+    plain, st, runs = timed(sim)
     progress(f"1024x1024x256: plain form {plain['ms_per_step'] / 1e3:.1f} s/step, solves "
              f"{plain['sweeps_per_solve']} sweeps")
     sim.close()
@@ -428,7 +418,7 @@ def largest_domain(args):
                  f"state; setup {t_init:.0f} s"),
         "plain": plain,
         "learned": learned,
-        "sweep": sweep_roofline(p, avg),
+        "sweep": sweep_roofline(p, avg, runs),
     }
 
 
@@ -473,12 +463,14 @@ def main():
     if args.warmup > 0:
         sim.step(args.warmup)
     torch.cuda.synchronize()
+    before = sim.solver_state()
     t0 = time.perf_counter()
     rc, st, recs = sim.step(args.steps, records=True, time_sweeps=True)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     if rc not in (les.LES_OK, les.LES_WARN_NOT_CONVERGED):
         raise SystemExit(f"les_step failed: {rc}")
+    runs = solver_runs(before, sim.solver_state())
 
     K = p["n_subiter"]
     sweeps_step = st["sweeps_total"] / args.steps
@@ -519,7 +511,7 @@ def main():
         "not_converged": st["not_converged"],
         "res_rel_max": st["res_rel_max"],
         "cfl": diag["cfl"],
-        "roofline": sweep_roofline(p, avg_sweep),
+        "roofline": sweep_roofline(p, avg_sweep, runs),
     }
     progress(f"{p['nx']}x{p['ny']}x{p['nz']}: plain form {value:.1f} Mcell-steps/s")
     if p["init"] != "cloud_layer":
