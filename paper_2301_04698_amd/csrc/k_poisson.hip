@@ -808,15 +808,17 @@ void launch_extrapolate(const Grid &g, const Profiles<T> &P, const T *p, const T
   extrapolate_kernel<T><<<blocks_for(g.n), kBlock, 0, s>>>(g, P, p, p_prev, phi0);
 }
 
-// Blocks of the guess/returned-residual kernel: one x row each at a time,
-// enough of them to keep every CU's memory pipes busy; 2 x 4096 partials fit
-// the partial buffer.
-// Blocks of guess_residual_kernel: at least its four x rows at a time each
-// (fewer rows are read again for nothing: 64 x 64 x 64 FP32 19.6 us with the
-// most blocks, 8.0 us with 1024), a multiple of 8 for the XCDs.
-constexpr int kResidualBlocks = 4096;  // at most
+// Blocks of guess_residual_kernel: its four x rows at a time each (fewer are
+// read again for nothing: 64 x 64 x 64 FP32 19.6 us with the most blocks, 8.0 us
+// with 1024), but a row each on grids that give no more than two blocks to a CU
+// so (51200 x 1 x 16 FP64: a kept guess solved in one sweep 517 us with two rows
+// a block, 474 with one); a multiple of 8 for the XCDs.
+constexpr int kFewRows = 512;
+constexpr int kResidualBlocks = 4096;  // at most; 2 x 4096 partials fit the buffer
 inline int residual_blocks(const Grid &g) {
-  return (int)std::min<int64_t>(kResidualBlocks, ((int64_t)g.ny * g.nz + 31) / 32 * 8);
+  const int64_t rows = (int64_t)g.ny * g.nz;
+  if (rows <= kFewRows) return (int)((rows + 7) / 8 * 8);
+  return (int)std::min<int64_t>(kResidualBlocks, (rows + 31) / 32 * 8);
 }
 static_assert(2 * kResidualBlocks <= kPartials, "residual partials exceed the buffer");
 
