@@ -810,10 +810,11 @@ void launch_extrapolate(const Grid &g, const Profiles<T> &P, const T *p, const T
 
 // Blocks of guess_residual_kernel: its four x rows at a time each (fewer are
 // read again for nothing: 64 x 64 x 64 FP32 19.6 us with the most blocks, 8.0 us
-// with 1024), but a row each on grids that give no more than two blocks to a CU
-// so (51200 x 1 x 16 FP64: a kept guess solved in one sweep 517 us with two rows
-// a block, 474 with one); a multiple of 8 for the XCDs.
-constexpr int kFewRows = 512;
+// with 1024), but a row each on grids of so few that most CUs would be idle
+// (51200 x 1 x 16 FP64: a kept guess solved in one sweep 517 us with two rows a
+// block, 474 with one; 1024 x 1 x 128 112 and 104; but 2000 x 1 x 300 148 and
+// 156); a multiple of 8 for the XCDs.
+constexpr int kFewRows = 128;
 constexpr int kResidualBlocks = 4096;  // at most; 2 x 4096 partials fit the buffer
 inline int residual_blocks(const Grid &g) {
   const int64_t rows = (int64_t)g.ny * g.nz;
