@@ -270,9 +270,11 @@ typedef struct les_diag {
 
 /* How the sweeps of a handle's solves run, and how they have run so far. */
 typedef struct les_solver_info {
-  int32_t resident_blocks;   /* > 0: a solve (of a cap of at most 2^20 sweeps)
-                                is one launch of so many blocks, its iterates
-                                resident on the chip; 0: launch by launch */
+  int32_t resident_blocks;   /* > 0: a solve (of a cap of at most 2^20 sweeps,
+                                not of a fixed count below 6 without a guess or
+                                LES_MEAN_EXACT) is one launch of so many
+                                blocks, its iterates resident on the chip; 0:
+                                launch by launch */
   int32_t sweeps_per_launch; /* launch by launch: at most so many in one */
   int64_t resident_passes;   /* passes of sweeps that ran resident to their
                                 end (a solve repeated or continued has more

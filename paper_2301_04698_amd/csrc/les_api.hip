@@ -475,6 +475,13 @@ bool resident_fits(const les_handle *h) {
 // the sweeps of a solve, and a solve that never converges should not hold
 // the GPU for longer than some seconds.
 constexpr int kResidentMaxSweeps = 1 << 20;
+// So do fixed counts of fewer sweeps than this without a guess and without
+// LES_MEAN_EXACT: a resident launch starts some 20 us later and a sweep is 3 to
+// 10 us shorter; with a guess, or where the iterate is assembled afterwards, one
+// read-back less makes up for it.  Whole solves of 1, 4 and 6 sweeps resident and
+// launch by launch: 64 x 64 x 64 FP32 67, 72, 76 and 50, 61, 70 us; with exact
+// parts 107, 113, 116 and 103, 116, 125 (4 x 4 x 4: 77, 88, 91 and 93, 102, 108).
+constexpr int kResidentMinSweeps = 6;
 
 // Centred right-hand side of a solve into F_RHS (rhs_in may be F_RHS
 // itself): the mean removed and, with the horizontally uniform part solved
@@ -828,6 +835,7 @@ int solve_prepared(les_handle *h, View<T> &V, const T *guess, bool gated, int fi
   SolveCtl r;
   T *phi = nullptr;
   double res2 = 0.0;
+  if (!guess && !V.vert && fixed > 0 && fixed < kResidentMinSweeps) V.res = false;
   // a kept guess's budget, as the cap of its sweeps (0: none)
   int cap = 0;
   if (guess && gated && fixed == 0 && budget > 0) {

@@ -38,7 +38,7 @@ def starts(sim, rhs):
     noise = torch.from_numpy(li.random_field(SHAPE, seed=6)).to(exact)
     near = (exact + 1e-2 * exact.abs().max().item() * noise).contiguous()
     return [(None, False, 0, 0), (near, True, 0, 0), (near, 2, 400, 0), (1e3 * near, 2, 400, 0),
-            (near, 2, 7, 0), (exact, 2, 50, 0), (near, True, 0, 5), (None, False, 0, 31)]
+            (near, 2, 7, 0), (exact, 2, 50, 0), (near, True, 0, 9), (None, False, 0, 31)]
 
 
 def solve(sim, rhs, start):
