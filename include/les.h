@@ -116,8 +116,12 @@ typedef struct les_config {
   int32_t satadj_maxit;         /* secant iteration cap */
   int32_t sweeps_per_launch;    /* Poisson sweeps fused per kernel launch, 0..2
                                    (0: default, every sweep of a solve in one
-                                   launch where the grid fits the chip, else 1);
-                                   results do not depend on it */
+                                   launch where the grid fits the chip and is
+                                   faster so, else three where their tiles are
+                                   used well, else one; 2: one where two have no
+                                   room for their residual sums; see
+                                   les_solver_plan); results do not depend on
+                                   it */
   double dx, dy, dz, dt;        /* m, m, m, s; all > 0 */
   double poisson_tol;           /* stop when ||rhs - L phi||_2 <= tol ||rhs||_2 */
   double jacobi_omega;          /* 0 selects 2/(mu_min+mu_max) */
@@ -216,7 +220,8 @@ typedef struct les_step_opts {
                                    per-solve sweep counts to apply exactly */
   les_solve_stats *records;     /* host, nsteps*n_subiter entries or NULL */
   int32_t time_sweeps;          /* 1: time runs of consecutive plain sweeps
-                                   (between residual checks) with HIP events */
+                                   (between residual checks; a resident solve:
+                                   all of its sweeps) with HIP events */
   int32_t reserved;
   void *dump_rhs;               /* device, n_subiter*n elements or NULL: the
                                    right-hand sides the sweeps of the call's
@@ -305,7 +310,8 @@ size_t les_workspace_bytes(const les_config *cfg);
  * 7..9 u,v,w at n+1/2, 10 b^{n+1/2}, 11 b_mid, 12 ql_mid, 13 c_pm*Pi (mid),
  * 14 nu scalars, 15 nu momentum, 16 radiative heating, 17 Poisson rhs,
  * 18..21 Poisson iterate buffers 0..3, 22 pressure of the previous step,
- * 23 starting iterate of a guessed solve, 24 its defect right-hand side. */
+ * 23 starting iterate of a guessed solve, 24 its defect right-hand side (in 19
+ * where the solve runs resident). */
 int les_workspace_offset(const les_config *cfg, int32_t field, size_t *offset);
 
 /* Validates cfg and buffers, computes the reference state (Sec. 2.1) and

@@ -9,8 +9,9 @@
 // channels are one 32-byte line.  Inference runs on the matrix cores with
 // FP32 accumulation: the 16 -> 16 and 16 -> 1 layers as implicit GEMMs
 // over pairs of in-plane taps (16 consecutive output cells per product),
-// the C -> 16 layer as one GEMM over (tap, channel) pairs.  The backward
-// pass is FP32 vector code (FP64 sums in the weight gradient).
+// the C -> 16 layer as one GEMM over (tap, channel) pairs.  So does the
+// backward pass, but for the last layer's activation gradient (vector code):
+// activation gradients as FP32 products, weight gradients as FP64 ones.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
